@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace fbp {
 
 // Read-only view of device data in the constant address space: uniform loads
@@ -180,16 +182,51 @@ struct ProjJob {
     int32_t N, K, D;
     float scale;          // pi/K
     int32_t T;            // pixels read per line
-    int32_t fast3;        // 1: three taps, 1 <= r <= 1.5 on every angle
     int32_t pad, pitch;   // zeros before each line; floats per padded line
 };
+// One base angle phi of the staged projector: a turn of the list's angle theta_{k0} by
+// t quarter turns back, so that a = cos(phi)/dt > 0 and |b| = |sin(phi)|/dt <= a.
+struct ProjAngle {
+    double a, b;
+    int32_t k0, k1;       // theta_{k1} = theta_{k0} + pi/2 (lists closed under +pi/2, else k0)
+    int32_t t, pad_;
+};
+struct ProjStagedJob {
+    const float* img;     // [n][N][N]
+    const float* tr;      // [n][N][N]: the transposed slices
+    float* sino;          // [n][K][D]
+    const ProjAngle* tab; // [n_base], neighbouring base angles consecutive
+    const float* wscale;  // [K] angle weight / (pi/K), or null
+    double half_pix, centre_det;
+    int32_t N, K, D, Dh;  // Dh = ceil(D / 2): bins walked per angle
+    int32_t n_base, n0;   // entries; the first n0 read the even turns (all of them in quarter-turn lists)
+    int32_t groups, groups0, bin_blocks;   // set by the launch
+    int32_t per;          // base angles per workgroup (set by the launch)
+    int32_t stratum;      // workgroups per stratum of the balanced order, 0: XCD order (set by the launch)
+    float scale;          // pi/K
+};
+constexpr int kProjWaves = 8;      // waves per workgroup: the most angles that share a window
+constexpr int kProjBins = 16;      // bins per workgroup and angle
+constexpr int kProjLines = 16;     // image rows staged at a time
+constexpr int kProjCells = 64;     // pixels staged per row
+constexpr int kProjMaxTaps = 4;    // taps per row (wider hats take project_kernel)
+// Most neighbouring base angles (a power of two) whose bins share a staged window in
+// every group of the table; 0: the windows do not fit (or T is above kProjMaxTaps).
+int project_group_angles(const std::vector<ProjAngle>& tab, int n0, int T, int N);
+// M = 4: quarter-turn list; M = 2: any list.
+hipError_t launch_project_staged(ProjStagedJob job, int M, int A_max, int T, bool fast3, int n_slices,
+                                 hipStream_t stream);
+// Transposed copies of n N x N slices.
+hipError_t launch_transpose(const float* img, float* out, int N, int n_slices, hipStream_t stream);
 // Tap count, kernel choice and padded-copy layout of a geometry's projector (cs as
 // in ProjJob); T == 0 when unsupported.
 struct ProjLayout {
     int T = 0;
     bool fast3 = false;
+    int M = 0, A = 0;          // staged projector: turned images per cell, angles per workgroup (0: not staged)
+    int n0 = 0;                // its entries that read the even turns
     int pad = 0, pitch = 0;
-    size_t slice_floats = 0;   // floats of the two padded planes of one slice
+    size_t slice_floats = 0;   // floats of the copies of one slice
     double margin = 0.0;       // fan beam: the margin its window bound holds on
 };
 ProjLayout project_layout(const double* cs, int K, int N);

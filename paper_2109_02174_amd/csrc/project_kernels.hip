@@ -7,23 +7,17 @@
 //     u_k(x, y) = (x cos(theta_k) + y sin(theta_k)) / dt + (D-1)/2,
 // with w_k = pi/K (or the angle-gap weights).
 //
-// It is computed gather-only, one lane per detector bin, walking image lines
-// across the ray: rows when |cos| >= |sin|, else columns.  The slice is first
-// copied twice, rows and transposed, each line padded with zeros on both sides
-// (pad P) and followed by one zero line, so that both walks read along memory and
-// a lane's window never needs a bounds test.  On a line the bin's ray crosses at
-// p* (pixel units along the line); the pixels with a nonzero weight are the
-// integers in (p* - r, p* + r), r = 1/|a| with a the slope of u along the line:
-// at most T = ceil(2r), read as T consecutive floats from floor(p* - r) + 1.
-// p* advances by the same step on every line, so it is carried in 32.32 fixed
-// point (integer part = window start, fraction = phase of the window), stepped
-// with a 64-bit integer add and re-anchored from FP64 every 256 lines; the hat
-// weights are FP32 functions of the phase.  A wave walks only the lines its 64
-// bins can reach; on those lines every bin of the wave lies within 65 r + 3
-// pixels of the image (it is within 63 bins of one that reaches it), which
-// bounds the pad.  Each bin is written once by its lane; no atomics; fixed
-// summation order (line by line).
+// It is computed gather-only, one lane per detector bin, walking image lines across
+// the ray.  On a line the bin's ray crosses at p* (pixel units along the line); the
+// pixels with a nonzero weight are the integers in (p* - r, p* + r), r = 1/|a| with a
+// the slope of u along the line: at most T = ceil(2r), T consecutive pixels from
+// floor(p* - r) + 1.  Each bin is written once; no atomics; fixed summation order.
+// Two forms: the staged projector (image rows through LDS, several bins per walk) for
+// up to four taps whose windows fit its LDS rows, and project_kernel for the rest.
 #include "fbp_internal.hpp"
+
+#include <algorithm>
+#include <cmath>
 
 namespace fbp {
 
@@ -33,11 +27,305 @@ constexpr int kProjThreads = 256;
 constexpr int kTrTile = 64;
 constexpr int kAnchorLines = 256;                   // FP64 re-anchoring period (power of 2)
 constexpr double kTwo32 = 4294967296.0;
+constexpr int kRawWord3 = 0x00020000;               // buffer resource word 3: 32-bit data, raw (stride 0)
+constexpr int kOffImage = 0x7FFFFFF0;               // byte offset past every image: reads as 0
 
-// Taps of one line: T > 0 fixed, T == 0 job.T at run time.  FAST3: three taps
-// with 1 <= r <= 1.5 on every angle (unit detector spacing), where the first tap
-// lies left of p* and the third right of it, so only the middle one needs |.|.
-template <int T, bool FAST3>
+// ---------------------------------------------------------------- staged projector
+//
+// A lane owns a bin of one base angle and walks image lines as above, but the lines
+// come from LDS, and each position and weight it makes serves two or four bins:
+//  * Turning the image by a quarter turn moves a projection to the angle a quarter
+//    turn on, bin by bin (u_{theta+pi/2}(R X) = u_theta(X), R(x, y) = (-y, x)), and
+//    turning it by a half reverses the bins.  So with I_m(X) = img(R^m X), the walk of
+//    bin j at a base angle phi gives, from I_0 .. I_3, the bins j and D-1-j at phi and
+//    at phi + pi/2 (M = 4: lists closed under +pi/2); any list has I_0 and I_2 (M = 2:
+//    bins j and D-1-j).  The base angle is the turn of theta with |tan phi| <= 1, so
+//    every walk runs along rows.  The rows of the turned images are rows of the image
+//    and of its transpose, read forwards or backwards: one transposed copy is the only
+//    extra memory.
+//  * A workgroup of eight waves owns A neighbouring base angles and kBins bins.  Per
+//    chunk of kLines image rows it stages the pixels those bins can reach as cells
+//    {I_0, I_1, I_2, I_3} (at most kCells a row: the host checks the group's bound), the
+//    next chunk's pixels loading while the current one is summed (double-buffered, one
+//    barrier per chunk).  A lane of a wave takes every fourth row (16 bins by 4 rows).
+//  * Positions are FP32, local to the staged window and anchored in FP64 per chunk.
+//    Weights are scaled by r = 1/a, which leaves three taps at 1 <= r <= 1.5 as 1 - f,
+//    r - |f - (2 - r)| and max(0, f + 2r - 3) of the phase f; the sum is scaled by a.
+//  * Every bin has 16 sums: rows = i + 4 q (mod 16) for lane row i and step q.  They
+//    are added in that order through LDS, whichever waves made them, so the number of
+//    angles per workgroup never changes a bit.  No atomics; each bin is written once.
+// Bound by VALU issue, with LDS reads close behind: a step of a wave (64 lane-rows, 256
+// bin-rows at M = 4) is 20 VALU instructions and three 16-byte LDS reads, and staging,
+// anchors and steps off the image add a quarter (512^2, 720 angles: 20.2 M VALU
+// instructions, 33 us at full issue; the staging loads taken out leave 38 of 39 us, the
+// LDS bank conflicts 35).  Measured there: 60 us one slice, 39 us a slice in stacks of
+// 16, against 111 and 87 us for one lane per bin reading padded copies from memory.
+// 16 bins by 4 rows per wave rather than 32 by 2: the blocks are half as large, four to
+// a CU for one slice; 4 or 2 angles instead of 8 stage more per bin (70 and 104 us).
+constexpr int kStThreads = 512;
+constexpr int kStWaves = kStThreads / 64;
+constexpr int kBins = kProjBins;                    // bins per workgroup and angle
+constexpr int kLines = kProjLines;                  // image rows per chunk
+constexpr int kCells = kProjCells;                  // staged pixels per row
+constexpr int kSteps = 4;                           // rows of a chunk a lane takes: kLines / (64 / kBins)
+static_assert(kBins * (kLines / kSteps) == 64 && kLines == 2 * kStWaves && kCells == 64, "staged projector layout");
+
+template <int M>
+struct Cell;
+template <>
+struct Cell<4> {
+    using type = float4;
+};
+template <>
+struct Cell<2> {
+    using type = float2;
+};
+template <>
+struct Cell<1> {
+    using type = float;
+};
+__device__ __forceinline__ void unpack(const float4& c, float (&v)[4]) { v[0] = c.x; v[1] = c.y; v[2] = c.z; v[3] = c.w; }
+__device__ __forceinline__ void unpack(const float2& c, float (&v)[2]) { v[0] = c.x; v[1] = c.y; }
+__device__ __forceinline__ void unpack(const float& c, float (&v)[1]) { v[0] = c; }
+__device__ __forceinline__ void pack(const float (&v)[4], float4& c) { c = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void pack(const float (&v)[2], float2& c) { c = make_float2(v[0], v[1]); }
+__device__ __forceinline__ void pack(const float (&v)[1], float& c) { c = v[0]; }
+
+// Loads of one chunk by one lane: pixel `px` of two rows of the M turned images, as
+//     I_0[l][p] = img[l][p]            I_1[l][p] = tr[N-1-l][p]
+//     I_2[l][p] = img[N-1-l][N-1-p]    I_3[l][p] = tr[l][N-1-p]
+// (tr the transposed image).  M = 4: all four; M = 2: I_s, I_{s+2}; M = 1: I_s alone.
+// Rows and pixels off the image read as 0 (range-checked buffer loads).
+template <int M>
+struct TurnRows {
+    __amdgpu_buffer_rsrc_t img, tr;
+    int N, s;
+    __device__ __forceinline__ TurnRows(const float* im, const float* t, int n, int sel) : N(n), s(sel) {
+        img = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(im), (short)0, n * n * 4, kRawWord3);
+        tr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(t), (short)0, n * n * 4, kRawWord3);
+    }
+    __device__ __forceinline__ float at(const __amdgpu_buffer_rsrc_t& b, int row, int off) const {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, off, row * N * 4, 0));
+    }
+    // pixel px < end of row l (uniform); pixels from `end` on are not loaded (0)
+    __device__ __forceinline__ void load(float (&v)[M], int l, int px, int end) const {
+        const bool in = (unsigned)px < (unsigned)min(N, end) && l < N;
+        const int fwd = in ? px * 4 : kOffImage, rev = in ? (N - 1 - px) * 4 : kOffImage;
+        const int la = l < N ? l : 0, lb = N - 1 - la;
+        if constexpr (M == 4) {
+            v[0] = at(img, la, fwd);
+            v[1] = at(tr, lb, fwd);
+            v[2] = at(img, lb, rev);
+            v[3] = at(tr, la, rev);
+        } else if constexpr (M == 2) {
+            v[0] = s ? at(tr, lb, fwd) : at(img, la, fwd);
+            v[1] = s ? at(tr, la, rev) : at(img, lb, rev);
+        } else {
+            v[0] = s == 0 ? at(img, la, fwd) : s == 1 ? at(tr, lb, fwd) : s == 2 ? at(img, lb, rev) : at(tr, la, rev);
+        }
+    }
+};
+
+// T taps; FAST3: T == 3 and 1 <= r <= 1.5 on every angle.  P: parts the rows of a chunk
+// are split over (P waves per angle, A = 8 / P angles per workgroup).
+template <int M, int T, bool FAST3, int P>
+__global__ __launch_bounds__(kStThreads) void project_staged_kernel(ProjStagedJob job) {
+    using C = typename Cell<M>::type;
+    constexpr int A = kStWaves / P;
+    constexpr int NS = kSteps / P;                  // steps of this wave
+    __shared__ __attribute__((aligned(16))) C win[2][kLines][kCells];
+    extern __shared__ int2 wlo_lds[];               // [chunks] first staged pixel and one past the last (equal: none)
+    const int per_slice = job.groups * job.bin_blocks;
+    // Workgroups of one stratum (one per CU) are dealt out in turn; every second stratum
+    // is taken backwards, so that a CU's workgroups add up to about the same work
+    int b = blockIdx.x;
+    if (job.stratum > 0) {
+        const int q = b / job.stratum;
+        if ((q & 1) && (q + 1) * job.stratum <= (int)gridDim.x) b = (2 * q + 1) * job.stratum - 1 - b;
+    } else {
+        b = xcd_logical(b, gridDim.x);
+    }
+    const int s = b / per_slice;
+    const int rest = b - s * per_slice;
+    // bin blocks from the middle of the detector outwards: the longest walks first
+    const int jb = job.bin_blocks - 1 - rest / job.groups;
+    const int g = rest - (rest / job.groups) * job.groups;
+    const int sel = g >= job.groups0 ? 1 : 0;       // M = 2: which pair of turns this group reads
+    const int first = sel ? job.n0 + (g - job.groups0) * job.per : g * job.per;
+    const int n_ang = min(job.per, (sel ? job.n_base : job.n0) - first);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = job.N, D = job.D;
+    const double half = job.half_pix, cd = job.centre_det;
+    const int j0 = jb * kBins;
+    const int nch = (N + kLines - 1) / kLines;
+
+    // windows of the chunks: first staged pixel over the group's angles, bins and rows
+    // (X = p* - r, linear in the bin and the row), or none when no pixel is reached
+    for (int c = tid; c < nch; c += kStThreads) {
+        double lo = INFINITY, hi = -INFINITY;
+        for (int i = 0; i < n_ang; ++i) {
+            const ProjAngle* e = job.tab + first + i;
+            const double inv = 1.0 / e->a, dl = -e->b * inv;
+            const double x = ((double)j0 - cd + e->b * half) * inv + half - inv + (double)(c * kLines) * dl;
+            const double run = (double)(kLines - 1) * dl;
+            lo = fmin(lo, x + fmin(0.0, run));
+            hi = fmax(hi, x + (double)(kBins - 1) * inv + fmax(0.0, run));
+        }
+        // taps of a lane: floor(X) + 1 .. floor(X) + T; one pixel of margin below for FP32
+        const bool none = hi + (double)(T + 1) < 0.0 || lo > (double)N;
+        const int w = none ? 0 : (int)floor(lo) - 1;
+        wlo_lds[c] = make_int2(w, none ? 0 : (int)floor(hi) + T + 2);
+    }
+
+    // this wave's angle, and this lane's bin and rows
+    const int ia = wave & (A - 1), part = wave / A;
+    const bool active = ia < n_ang;
+    const ProjAngle* e = job.tab + first + (active ? ia : 0);
+    const double inv_a = 1.0 / e->a, dl = -e->b * inv_a;
+    const int li = lane / kBins;                    // row of the lane within a step
+    const int j = j0 + (lane & (kBins - 1));
+    const double xj = ((double)j - cd + e->b * half) * inv_a + half - inv_a;   // X on row 0
+    const float r = (float)inv_a, r2 = (float)(2.0 - inv_a), r3 = (float)(2.0 * inv_a - 3.0);
+    float tap[T];                                   // 1 + m - r
+#pragma unroll
+    for (int m = 0; m < T; ++m) tap[m] = (float)((double)(m + 1) - inv_a);
+    float step[NS];                                 // X from row li of a chunk to the lane's row of step q
+#pragma unroll
+    for (int q = 0; q < NS; ++q) step[q] = (float)((double)(4 * (part + P * q)) * dl);
+    // smallest X of the angle's bins on a chunk's rows, from the chunk's first row on row 0
+    const double x_min = ((double)j0 - cd + e->b * half) * inv_a + half - inv_a + fmin(0.0, (double)(kLines - 1) * dl);
+
+    const size_t pix = (size_t)N * N;
+    const TurnRows<M> rows(job.img + (size_t)s * pix, job.tr + (size_t)s * pix, N, sel);
+    float pf[2][M];
+    auto load = [&](int c, int2 w) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) rows.load(pf[h], c * kLines + 2 * wave + h, w.x + lane, max(w.y, 0));
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) pack(pf[h], win[buf][2 * wave + h][lane]);
+    };
+    float acc[NS][M];
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int m = 0; m < M; ++m) acc[q][m] = 0.0f;
+    auto next = [&](int c, int2& w) {               // the next chunk with a window
+        for (++c; c < nch; ++c) {
+            const int2 v = wlo_lds[c];
+            w = make_int2(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y));
+            if (w.x != w.y) break;
+        }
+        return c;
+    };
+    auto compute = [&](int buf, int c, int wlo) {
+        // positions local to the angle's own window (not the group's, so that the grouping
+        // does not round them differently)
+        const double own = floor(fma((double)(c * kLines), dl, x_min)) - 1.0;
+        const float xr = (float)(fma((double)(c * kLines + li), dl, xj) - own);
+        const C* __restrict__ row0 = &win[buf][li + 4 * part][0] + ((int)own - wlo);
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const float x = xr + step[q];           // >= 1 up to rounding: truncation is floor
+            const int i = (int)x;
+            const float f = __builtin_amdgcn_fractf(x);
+            const C* __restrict__ px = row0 + 4 * P * q * kCells + i;
+            float w[T];
+            if constexpr (FAST3) {
+                w[0] = 1.0f - f;
+                w[1] = r - fabsf(f - r2);
+                w[2] = fmaxf(f + r3, 0.0f);
+            } else {
+#pragma unroll
+                for (int m = 0; m < T; ++m) w[m] = fmaxf(r - fabsf(f - tap[m]), 0.0f);
+            }
+#pragma unroll
+            for (int m = 0; m < T; ++m) {
+                float v[M];
+                unpack(px[m + 1], v);
+#pragma unroll
+                for (int z = 0; z < M; ++z) acc[q][z] = fmaf(w[m], v[z], acc[q][z]);
+            }
+        }
+    };
+    __syncthreads();                                // windows made
+    int2 w0 = make_int2(0, 0), w1 = w0;
+    int c = next(-1, w0);
+    if (c < nch) load(c, w0);
+    for (int buf = 0; c < nch; buf ^= 1) {
+        store(buf);
+        const int cn = next(c, w1);
+        if (cn < nch) load(cn, w1);
+        // one barrier per chunk: a wave stores into a buffer two chunks after reading it,
+        // and it passed the barrier between with every wave done reading
+        __syncthreads();
+        if (active) compute(buf, c, w0.x);
+        c = cn;
+        w0 = w1;
+    }
+
+    // the 16 sums of each bin, in step and row order
+    __syncthreads();
+    float* part_lds = reinterpret_cast<float*>(&win[0][0][0]);   // [A][kSteps][M][64]
+    static_assert(sizeof(float) * A * kSteps * M * 64 <= sizeof(win), "sums fit the windows");
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int m = 0; m < M; ++m) part_lds[((ia * kSteps + part + P * q) * M + m) * 64 + lane] = acc[q][m];
+    __syncthreads();
+    for (int o = tid; o < n_ang * M * kBins; o += kStThreads) {
+        const int bin = o & (kBins - 1), m = (o / kBins) % M, i = o / (kBins * M);
+        float sum = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kSteps; ++q)
+#pragma unroll
+            for (int z = 0; z < 64 / kBins; ++z) sum += part_lds[((i * kSteps + q) * M + m) * 64 + z * kBins + bin];
+        // turn m of the base angle: m = t is the angle itself, t + 1 (M = 4) a quarter turn
+        // on, t + 2 and t + 3 the same with the bins reversed
+        const ProjAngle* ea = job.tab + first + i;
+        const int turn = M == 4 ? (m - ea->t) & 3 : ((sel + 2 * m) - ea->t) & 3;
+        const int k = (turn & 1) ? ea->k1 : ea->k0;
+        const int jj = j0 + bin, out = (turn & 2) ? D - 1 - jj : jj;
+        if (jj < job.Dh && !((turn & 2) && out == jj)) {
+            const float wk = job.wscale ? job.wscale[k] * job.scale : job.scale;
+            job.sino[((size_t)s * job.K + k) * D + out] = sum * (float)ea->a * wk;
+        }
+    }
+}
+
+// Transposed copies of n N x N slices, 64 x 64 tiles through LDS.
+__global__ __launch_bounds__(256) void transpose_kernel(const float* __restrict__ img, float* __restrict__ out, int N,
+                                                        int tiles) {
+    __shared__ float tile[kTrTile][kTrTile + 1];
+    const int per = tiles * tiles;
+    const int s = blockIdx.x / per;
+    const int t = blockIdx.x - s * per;
+    const int r0 = (t / tiles) * kTrTile, c0 = (t % tiles) * kTrTile;
+    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    const float* src = img + (size_t)s * N * N;
+    float* dst = out + (size_t)s * N * N;
+#pragma unroll
+    for (int i = 0; i < kTrTile; i += 4)
+        if (r0 + ty + i < N && c0 + tx < N) tile[ty + i][tx] = src[(size_t)(r0 + ty + i) * N + c0 + tx];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kTrTile; i += 4)
+        if (c0 + ty + i < N && r0 + tx < N) dst[(size_t)(c0 + ty + i) * N + r0 + tx] = tile[tx][ty + i];
+}
+
+// ---------------------------------------------------------------- any detector spacing
+//
+// Taps counted at run time: the detectors whose windows are too wide to stage (five or
+// more pixels per line).  Rows when |cos| >= |sin|, else columns.  The slice is first
+// copied twice, rows and transposed, each line padded with zeros on both sides (pad P)
+// and followed by one zero line, so that both walks read along memory and a lane's
+// window never needs a bounds test.  p* advances by the same step on every line, so it
+// is carried in 32.32 fixed point (integer part = window start, fraction = phase of the
+// window), re-anchored from FP64 every 256 lines.  A wave walks only the lines its 64
+// bins can reach; on those every bin of the wave lies within 65 r + 3 pixels of the
+// image (it is within 63 bins of one that reaches it), which bounds the pad.
 __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjJob job) {
     // block b: (slice, angle, block of 256 bins), bins fastest
     const int nbj = (job.D + kProjThreads - 1) / kProjThreads;
@@ -48,7 +336,7 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjJob job) {
     if (jw >= job.D) return;                        // whole wave past the last bin
     const int j = jw + (threadIdx.x & 63);
     const int N = job.N;
-    const int taps = T > 0 ? T : job.T;
+    const int taps = job.T;
     const double c = job.cs[2 * k];                 // cos/dt
     const double sn = job.cs[2 * k + 1];            // sin/dt
     const double half = job.half_pix;               // (N-1)/2
@@ -97,81 +385,17 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjJob job) {
         };
         const uint64_t step = (uint64_t)(int64_t)llrint(dl * kTwo32);
         const uint32_t st_max = (uint32_t)(pitch - taps);
-        const float aa = (float)fabs(a);
-        const float na = (float)(-fabs(a) / kTwo32), pa = (float)(fabs(a) / kTwo32);
-        const float c1 = (float)(fabs(a) * (2.0 - r)), c2 = (float)(2.0 - 3.0 * fabs(a));
         const float sa = (float)(-a / kTwo32);
-        float cm[T > 0 ? T : 1];                    // a (1 - r + m): hat argument of tap m at phase 0
-        if constexpr (T > 0) {
-#pragma unroll
-            for (int m = 0; m < T; ++m) cm[m] = (float)(a * (1.0 - r + (double)m));
-        }
-        if constexpr (T > 0) {
-            auto load = [&](const float* ln, uint64_t x, float& ph, float (&v)[T]) {
-                const uint32_t st = min((uint32_t)(x >> 32), st_max);    // in bounds whatever x holds
-                ph = (float)(uint32_t)x;                                  // phase * 2^32
-                const float* __restrict__ px = ln + st;
-#pragma unroll
-                for (int m = 0; m < T; ++m) v[m] = px[m];        // one T-dword load
-            };
-            auto accumulate = [&](float ph, const float (&v)[T]) {
-                if constexpr (FAST3) {
-                    const float w0 = fmaf(na, ph, aa);                    // |a| (1 - phase)
-                    const float w1 = 1.0f - fabsf(fmaf(na, ph, c1));
-                    const float w2 = __builtin_amdgcn_fmed3f(fmaf(pa, ph, c2), 0.0f, 1.0f);
-                    acc = fmaf(w0, v[0], acc);
-                    acc = fmaf(w1, v[1], acc);
-                    acc = fmaf(w2, v[2], acc);
-                } else {
-#pragma unroll
-                    for (int m = 0; m < T; ++m) {
-                        const float t = fmaf(sa, ph, cm[m]);              // a (tap - p*)
-                        const float w = __builtin_amdgcn_fmed3f(1.0f - fabsf(t), 0.0f, 1.0f);
-                        acc = fmaf(w, v[m], acc);
-                    }
-                }
-            };
-            // lines in runs of kAnchorLines from an FP64 anchor; four lines per round,
-            // all four loads issued before the first line's weights
-            for (int l0 = l_lo; l0 <= l_hi; l0 += kAnchorLines) {
-                const int l1 = min(l0 + kAnchorLines - 1, l_hi);
-                uint64_t x = anchor(l0);
-                int l = l0;
-                for (; l + 3 <= l1; l += 4) {
-                    float ph[4];
-                    float v[4][T];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        load(line + u * pitch, x, ph[u], v[u]);
-                        x += step;
-                        asm volatile("" : "+v"(x));         // one 64-bit add per line, no unrolled copies
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) accumulate(ph[u], v[u]);
-                    line += 4 * pitch;
-                }
-                for (; l <= l1; ++l) {
-                    float ph;
-                    float v[T];
-                    load(line, x, ph, v);
-                    accumulate(ph, v);
-                    x += step;
-                    asm volatile("" : "+v"(x));
-                    line += pitch;
-                }
-            }
-        } else {
-            uint64_t x = anchor(l_lo);
-            for (int l = l_lo; l <= l_hi; ++l, line += pitch) {
-                if (l != l_lo) x = ((l & (kAnchorLines - 1)) == 0) ? anchor(l) : x + step;
-                const uint32_t st = min((uint32_t)(x >> 32), st_max);
-                const float ph = (float)(uint32_t)x;
-                const float* __restrict__ px = line + st;
-                for (int m = 0; m < taps; ++m) {
-                    const float t = fmaf(sa, ph, (float)(a * (1.0 - r + (double)m)));
-                    const float w = __builtin_amdgcn_fmed3f(1.0f - fabsf(t), 0.0f, 1.0f);
-                    acc = fmaf(w, px[m], acc);
-                }
+        uint64_t x = anchor(l_lo);
+        for (int l = l_lo; l <= l_hi; ++l, line += pitch) {
+            if (l != l_lo) x = ((l & (kAnchorLines - 1)) == 0) ? anchor(l) : x + step;
+            const uint32_t st = min((uint32_t)(x >> 32), st_max);    // in bounds whatever x holds
+            const float ph = (float)(uint32_t)x;                     // phase * 2^32
+            const float* __restrict__ px = line + st;
+            for (int m = 0; m < taps; ++m) {
+                const float t = fmaf(sa, ph, (float)(a * (1.0 - r + (double)m)));   // a (tap - p*)
+                const float w = __builtin_amdgcn_fmed3f(1.0f - fabsf(t), 0.0f, 1.0f);
+                acc = fmaf(w, px[m], acc);
             }
         }
     }
@@ -296,7 +520,8 @@ ProjLayout project_layout(const double* cs, int K, int N) {
     }
     ProjLayout L;
     L.fast3 = r_min >= 1.0 && r_max <= 1.5;
-    L.T = L.fast3 ? 3 : (int)ceil(2.0 * r_max);
+    L.T = L.fast3 ? 3 : (int)fmin(ceil(2.0 * r_max), 1e9);
+    L.slice_floats = (size_t)N * (size_t)N;         // the transposed copy (staged projector)
     const double pad = ceil(65.0 * r_max) + L.T + 4.0;
     const double pitch = (double)N + 2.0 * pad;
     if (!(pitch < 1e9)) {
@@ -305,8 +530,94 @@ ProjLayout project_layout(const double* cs, int K, int N) {
     }
     L.pad = (int)pad;
     L.pitch = (int)pitch;
-    L.slice_floats = (size_t)2 * (size_t)(N + 1) * (size_t)L.pitch;
     return L;
+}
+
+// The staged window of a group of neighbouring base angles (see project_staged_kernel):
+// a bin of one of them that crosses row y at p, |dp/dphi| = |v| / cos phi with v the
+// distance of (p, y) from the foot of the ray, at most N/sqrt(2) plus the window beyond
+// the image.  Pixels: 15 bin steps of r, 15 rows of slope |tan phi|, the spread over the
+// group's angles, T taps, and the rounding margins.
+int project_group_angles(const std::vector<ProjAngle>& tab, int n0, int T, int N) {
+    if (T > kProjMaxTaps) return 0;
+    for (int A = kProjWaves; A >= 1; A >>= 1) {
+        bool fits = true;
+        for (int part = 0; part < 2 && fits; ++part) {
+            const int lo = part ? n0 : 0, hi = part ? (int)tab.size() : n0;
+            for (int i = lo; i < hi && fits; i += A) {
+                double r = 0.0, slope = 0.0, sec = 0.0, p0 = INFINITY, p1 = -INFINITY;
+                for (int q = i; q < std::min(i + A, hi); ++q) {
+                    const double phi = std::atan2(tab[q].b, tab[q].a);
+                    r = std::max(r, 1.0 / tab[q].a);
+                    slope = std::max(slope, std::fabs(tab[q].b) / tab[q].a);
+                    sec = std::max(sec, 1.0 / std::cos(phi));
+                    p0 = std::min(p0, phi);
+                    p1 = std::max(p1, phi);
+                }
+                const double spread = (p1 - p0) * sec * (0.70710678118654752 * N + kProjCells + kProjLines);
+                fits = (kProjBins - 1) * r + (kProjLines - 1) * slope + spread + T + 4.0 <= (double)kProjCells;
+            }
+        }
+        if (fits) return A;
+    }
+    return 0;
+}
+
+template <int M, int T, bool FAST3>
+hipError_t launch_staged_parts(const ProjStagedJob& job, int A, dim3 grid, size_t lds, hipStream_t stream) {
+    const dim3 block(kStThreads);
+    switch (A) {
+        case 8: return launch_kernel(project_staged_kernel<M, T, FAST3, 1>, grid, block, lds, stream, job);
+        case 4: return launch_kernel(project_staged_kernel<M, T, FAST3, 2>, grid, block, lds, stream, job);
+        default: return launch_kernel(project_staged_kernel<M, T, FAST3, 4>, grid, block, lds, stream, job);
+    }
+}
+
+template <int M>
+hipError_t launch_staged_taps(const ProjStagedJob& job, int A, int T, bool fast3, dim3 grid, size_t lds,
+                              hipStream_t stream) {
+    if (fast3) return launch_staged_parts<M, 3, true>(job, A, grid, lds, stream);
+    switch (T) {
+        case 1: return launch_staged_parts<M, 1, false>(job, A, grid, lds, stream);
+        case 2: return launch_staged_parts<M, 2, false>(job, A, grid, lds, stream);
+        case 3: return launch_staged_parts<M, 3, false>(job, A, grid, lds, stream);
+        default: return launch_staged_parts<M, 4, false>(job, A, grid, lds, stream);
+    }
+}
+
+hipError_t launch_project_staged(ProjStagedJob job, int M, int A_max, int T, bool fast3, int n_slices,
+                                 hipStream_t stream) {
+    if (n_slices <= 0) return hipSuccess;
+    if (T < 1 || T > kProjMaxTaps || A_max < 1 || A_max > kProjWaves || (M != 2 && M != 4) || (fast3 && T != 3))
+        return hipErrorInvalidValue;
+    job.Dh = (job.D + 1) / 2;
+    job.bin_blocks = (job.Dh + kBins - 1) / kBins;
+    // Angles per workgroup: as many as share a window, unless that leaves fewer than two
+    // workgroups per CU (the same bits either way)
+    int A = A_max;
+    auto blocks_of = [&](int a) {
+        job.groups0 = (job.n0 + a - 1) / a;
+        job.groups = job.groups0 + (job.n_base - job.n0 + a - 1) / a;
+        return (int64_t)job.groups * job.bin_blocks * n_slices;
+    };
+    while (A > 2 && blocks_of(A) < 2 * (int64_t)current_device_cus()) A >>= 1;
+    const int64_t blocks = blocks_of(A);
+    job.per = A;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    // Short stacks: the balanced order; long ones: whole slices to one XCD, whose L2 they share
+    job.stratum = n_slices < 8 ? current_device_cus() : 0;
+    const size_t lds = sizeof(int2) * (size_t)((job.N + kLines - 1) / kLines);
+    const dim3 grid((unsigned)blocks);
+    return M == 4 ? launch_staged_taps<4>(job, A, T, fast3, grid, lds, stream)
+                  : launch_staged_taps<2>(job, A, T, fast3, grid, lds, stream);
+}
+
+hipError_t launch_transpose(const float* img, float* out, int N, int n_slices, hipStream_t stream) {
+    if (n_slices <= 0) return hipSuccess;
+    const int tiles = (N + kTrTile - 1) / kTrTile;
+    const int64_t blocks = (int64_t)tiles * tiles * n_slices;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    return launch_kernel(transpose_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, img, out, N, tiles);
 }
 
 hipError_t launch_project(const ProjJob& job, int n_slices, hipStream_t stream) {
@@ -314,18 +625,7 @@ hipError_t launch_project(const ProjJob& job, int n_slices, hipStream_t stream) 
     if (job.T < 1 || job.pitch < job.N + 2 * job.T || job.pad < job.T) return hipErrorInvalidValue;
     const int64_t blocks = (int64_t)((job.D + kProjThreads - 1) / kProjThreads) * job.K * n_slices;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(kProjThreads);
-    if (job.fast3) {
-        if (job.T != 3) return hipErrorInvalidValue;
-        return launch_kernel(project_kernel<3, true>, grid, block, 0, stream, job);
-    }
-    switch (job.T) {
-        case 1: return launch_kernel(project_kernel<1, false>, grid, block, 0, stream, job);
-        case 2: return launch_kernel(project_kernel<2, false>, grid, block, 0, stream, job);
-        case 3: return launch_kernel(project_kernel<3, false>, grid, block, 0, stream, job);
-        case 4: return launch_kernel(project_kernel<4, false>, grid, block, 0, stream, job);
-        default: return launch_kernel(project_kernel<0, false>, grid, block, 0, stream, job);
-    }
+    return launch_kernel(project_kernel, dim3((unsigned)blocks), dim3(kProjThreads), 0, stream, job);
 }
 
 hipError_t launch_fan_project(const FanProjJob& job, int n_slices, hipStream_t stream) {

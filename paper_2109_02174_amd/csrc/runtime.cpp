@@ -142,6 +142,8 @@ struct PartBuffer {
 struct ProjScratch {
     ProjLayout layout;
     float* ptr = nullptr;
+    ProjAngle* d_tab = nullptr;   // base angles of the staged projector
+    int n_base = 0;
     int slices = 0;
     hipEvent_t free_ev = nullptr;
     bool recorded = false;
@@ -601,6 +603,57 @@ ProjLayout fan_project_layout(const Plan& p) {
     L.pad = T + 2;                       // >= every line's tap count, whatever its rounding
     L.pitch = p.N + 2 * L.pad;
     L.slice_floats = (size_t)2 * (size_t)(p.N + 1) * (size_t)L.pitch;
+    return L;
+}
+
+// Base angles of the staged projector: each angle (for quarter-turn lists each of the
+// first K/2) turned back by t quarter turns into |tan phi| <= 1, cos phi > 0.  Sorted by
+// phi, so that neighbouring angles, whose windows overlap, are consecutive; lists without
+// quarter turns put the entries that read the even turns (t = 0, 2) first.
+std::vector<ProjAngle> project_base_angles(const Plan& p, bool quarter, int* n0) {
+    const int n = quarter ? p.K / 2 : p.K;
+    std::vector<ProjAngle> tab((size_t)n);
+    for (int k = 0; k < n; ++k) {
+        const double c = p.cs[2 * (size_t)k], s = p.cs[2 * (size_t)k + 1];
+        ProjAngle& e = tab[(size_t)k];
+        e = ProjAngle{};
+        if (std::fabs(c) >= std::fabs(s)) {
+            e.t = c > 0.0 ? 0 : 2;
+            e.a = std::fabs(c);
+            e.b = c > 0.0 ? s : -s;
+        } else {
+            e.t = s > 0.0 ? 1 : 3;
+            e.a = std::fabs(s);
+            e.b = s > 0.0 ? -c : c;
+        }
+        e.k0 = k;
+        e.k1 = quarter ? k + p.K / 2 : k;
+    }
+    auto odd = [&](const ProjAngle& e) { return !quarter && (e.t & 1) != 0; };
+    std::stable_sort(tab.begin(), tab.end(), [&](const ProjAngle& x, const ProjAngle& y) {
+        if (odd(x) != odd(y)) return odd(y);
+        return x.b * y.a < y.b * x.a;                // tan phi
+    });
+    *n0 = (int)std::count_if(tab.begin(), tab.end(), [&](const ProjAngle& e) { return !odd(e); });
+    return tab;
+}
+
+// Kernel and scratch layout of a parallel-beam projector: the staged one where a base
+// angle's window fits, else padded copies.
+ProjLayout parallel_project_layout(const Plan& p, std::vector<ProjAngle>* tab) {
+    ProjLayout L = project_layout(p.cs.data(), p.K, p.N);
+    if (L.T == 0) return L;
+    const bool quarter = quarter_turn_symmetric(p.angles);
+    int n0 = 0;
+    *tab = project_base_angles(p, quarter, &n0);
+    L.A = project_group_angles(*tab, n0, L.T, p.N);
+    if (L.A > 0) {
+        L.M = quarter ? 4 : 2;
+        L.n0 = n0;
+    } else {
+        tab->clear();
+        L.slice_floats = (size_t)2 * (size_t)(p.N + 1) * (size_t)L.pitch;
+    }
     return L;
 }
 
@@ -2100,14 +2153,23 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
     ProjScratch& ps = p->proj;
     std::lock_guard<std::mutex> lock(ps.mu);
     if (!ps.ptr) {
-        ps.layout = fan ? fan_project_layout(*p) : project_layout(p->cs.data(), p->K, p->N);
+        std::vector<ProjAngle> tab;
+        ps.layout = fan ? fan_project_layout(*p) : parallel_project_layout(*p, &tab);
         if (ps.layout.T == 0) return FBP_EUNSUPPORTED;
         const size_t slice_bytes = sizeof(float) * ps.layout.slice_floats;
         const int slices = (int)std::max<size_t>(1, std::min<size_t>(16, ((size_t)256 << 20) / slice_bytes));
         hipError_t e = hipMalloc(&ps.ptr, slice_bytes * (size_t)slices);
+        if (e == hipSuccess && !tab.empty()) {
+            e = hipMalloc(&ps.d_tab, sizeof(ProjAngle) * tab.size());
+            if (e == hipSuccess)
+                e = hipMemcpy(ps.d_tab, tab.data(), sizeof(ProjAngle) * tab.size(), hipMemcpyHostToDevice);
+            ps.n_base = (int)tab.size();
+        }
         if (e == hipSuccess) e = hipEventCreateWithFlags(&ps.free_ev, hipEventDisableTiming);
         if (e != hipSuccess) {
+            if (ps.d_tab) (void)hipFree(ps.d_tab);
             if (ps.ptr) (void)hipFree(ps.ptr);
+            ps.d_tab = nullptr;
             ps.ptr = nullptr;
             return hip_fail(e, "hipMalloc (projector copies)", FBP_ENOMEM);
         }
@@ -2116,6 +2178,7 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
     const hipStream_t s = (hipStream_t)hip_stream;
     const ProjLayout& L = ps.layout;
     ProjJob j{};
+    ProjStagedJob sj{};
     FanProjJob fj{};
     if (fan) {
         fj.pimg = ps.ptr;
@@ -2131,6 +2194,18 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
         fj.pad = L.pad;
         fj.pitch = L.pitch;
         fj.scale = (float)(2.0 * kPi / (double)p->K);
+    } else if (L.A > 0) {
+        sj.tr = ps.ptr;
+        sj.tab = ps.d_tab;
+        sj.wscale = p->d_wscale;
+        sj.half_pix = 0.5 * (double)(p->N - 1);
+        sj.centre_det = 0.5 * (double)(p->D - 1);
+        sj.N = p->N;
+        sj.K = p->K;
+        sj.D = p->D;
+        sj.n_base = ps.n_base;
+        sj.n0 = L.n0;
+        sj.scale = (float)(kPi / (double)p->K);
     } else {
         j.pimg = ps.ptr;
         j.cs = p->d_cs;
@@ -2142,7 +2217,6 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
         j.D = p->D;
         j.scale = (float)(kPi / (double)p->K);
         j.T = L.T;
-        j.fast3 = L.fast3 ? 1 : 0;
         j.pad = L.pad;
         j.pitch = L.pitch;
     }
@@ -2150,11 +2224,17 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
     if (ps.recorded) FBP_TRY_HIP(hipStreamWaitEvent(s, ps.free_ev, 0));
     for (int32_t i0 = 0; i0 < n_slices; i0 += ps.slices) {
         const int n = std::min<int32_t>(ps.slices, n_slices - i0);
-        hipError_t e = launch_pad(d_image + (size_t)i0 * is, ps.ptr, p->N, L.pad, L.pitch, n, s);
+        const float* src = d_image + (size_t)i0 * is;
+        hipError_t e = L.A > 0 ? launch_transpose(src, ps.ptr, p->N, n, s)
+                               : launch_pad(src, ps.ptr, p->N, L.pad, L.pitch, n, s);
         if (e == hipSuccess) {
             if (fan) {
                 fj.sino = d_sino + (size_t)i0 * qs;
                 e = launch_fan_project(fj, n, s);
+            } else if (L.A > 0) {
+                sj.img = src;
+                sj.sino = d_sino + (size_t)i0 * qs;
+                e = launch_project_staged(sj, L.M, L.A, L.T, L.fast3, n, s);
             } else {
                 j.sino = d_sino + (size_t)i0 * qs;
                 e = launch_project(j, n, s);
