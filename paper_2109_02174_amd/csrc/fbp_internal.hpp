@@ -234,8 +234,28 @@ hipError_t launch_project(const ProjJob& job, int n_slices, hipStream_t stream);
 // Padded row and column copies of n N x N slices into out (n * slice_floats floats).
 hipError_t launch_pad(const float* img, float* out, int N, int pad, int pitch, int n_slices, hipStream_t stream);
 
-// Fan-beam forward projector (the adjoint of the fan-beam backprojector), reading
-// the same padded copies.
+// Staged fan-beam forward projector.  A table entry is a base view: a = cos, b = sin of
+// its angle, turned back by t quarter turns from view k0 (M = 4: a view of the first K/4
+// and its three quarter turns; M = 1: every view as it is, t = 0); neighbours consecutive.
+struct FanStagedJob {
+    const float* turned;  // the turned images of the slices (launch_turn)
+    float* sino;          // [n][K][D]
+    const ProjAngle* tab; // [n_base]
+    double R, inv_ds;     // source distance, 1 / bin width
+    double half_pix, centre_det;
+    int32_t N, K, D, n_base;
+    int32_t n_slices, groups, bin_blocks, stratum;   // set by the launch (as in ProjStagedJob)
+    int32_t most;         // views of the largest group (set by the launch)
+    float scale;          // 2 pi / K
+};
+// Most views per workgroup whose windows fit for every group of the table; 0: not staged.
+int fan_group_views(const std::vector<ProjAngle>& tab, int N, int D, double R, double ds);
+size_t fan_turned_floats(int N);   // of one slice
+hipError_t launch_turn(const float* img, float* turned, int N, int M, int n_slices, hipStream_t stream);
+hipError_t launch_fan_project_staged(FanStagedJob job, int M, int A_max, int n_slices, hipStream_t stream);
+
+// Fan-beam forward projector for the geometries that are not staged, reading the same
+// padded copies as project_kernel.
 struct FanProjJob {
     const float* pimg;    // padded copies, [n][2][N+1][pitch] (launch_pad)
     float* sino;          // [n][K][D]

@@ -18,6 +18,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace fbp {
 
@@ -291,6 +292,368 @@ __global__ __launch_bounds__(kStThreads) void project_staged_kernel(ProjStagedJo
         if (jj < job.Dh && !((turn & 2) && out == jj)) {
             const float wk = job.wscale ? job.wscale[k] * job.scale : job.scale;
             job.sino[((size_t)s * job.K + k) * D + out] = sum * (float)ea->a * wk;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- staged fan-beam projector
+//
+// The adjoint of the fan-beam backprojection
+//     img(X) = (2 pi / K) sum_k (R / L_k)^2 Q~_k(u_k(X)),  L_k = R - (x cos b_k + y sin b_k),
+//     u_k(X) = R (-x sin b_k + y cos b_k) / (L_k ds) + (D-1)/2
+// (Kak & Slaney 1988, ch. 3), i.e.
+//     sino[k][j] = (2 pi / K) sum_X img(X) (R / L_k)^2 max(0, 1 - |u_k(X) - j|),
+// in the staged projector's manner: a lane owns a bin of one base view and walks rows
+// that come from LDS; the four turned images (M = 4: lists closed under quarter turns)
+// and S slices share every position and weight.  What the fan beam changes:
+//  * Turning the image by a quarter turn moves bin j of a view to bin j of the view a
+//    quarter turn on; there are no reversed bins.  M = 4 serves views b + m pi/2 from
+//    I_0 .. I_3, M = 1 (any other list) the view itself from one turned image.
+//  * The turn is chosen per (views of the workgroup, its bins) by the direction of the
+//    rays, not per view, so that every walked ray runs within about 45 degrees of the
+//    columns whatever the fan's opening: windows stay narrow and pixels few per row.
+//  * On a row the pixels with a nonzero weight lie exactly between the crossings of the
+//    neighbouring rays, u = j - 1 and u = j + 1.  Every crossing is affine in the row, so
+//    the first tap follows ray j - 1 in FP32 steps anchored in FP64 per chunk, and the
+//    tap count is a number of the chunk (workgroup-uniform), from 1 to kFanTaps.
+//  * With d the tap's distance from ray j along the row, l the ray's depth L/R there:
+//    L/R at the tap is l + d L'/R and u - j = d E'/R / (L/R); one reciprocal per tap
+//    serves the hat and the (R/L)^2 weight, for M S pixels.
+//  * The turned images are laid out once per call with a border of zeros, M = 4 as cells
+//    {I_0, I_1, I_2, I_3}, so that staging is one 16-byte load and one LDS store per cell.
+// Bound by VALU issue: per tap six instructions, a quarter-rate reciprocal and M S
+// multiply-adds (512^2, 720 views, two slices: 58.6 M wave instructions, 95 of 160 us at
+// full issue; LDS 66 us).  Measured there: 160 us, against 1450 us for one lane per bin
+// reading padded copies from memory.  Eight views a workgroup rather than four: 160 and
+// 201 us (a staged cell serves twice the bins); two slices rather than one: 160 and 203 us.
+// 16 rows of at most 64 cells, which only two views fit, gathered from the image and its
+// transpose a pixel at a time: 277 us, 145 of them in staging alone.
+constexpr int kFanTaps = 6;                         // most taps per row (wider hats take fan_project_kernel)
+constexpr int kFanLines = 8;                        // image rows per chunk
+constexpr int kFanCells = 96;                       // staged pixels per row
+constexpr int kFanBorder = kFanCells;               // zeros on both sides of a row of the turned images
+constexpr double kFanMinDepth = 16.0;               // depths are kept above this (the image lies beyond it)
+
+struct FanRay {                                     // crossing of ray u = cd - g with row l: p0 + l dp (pixels)
+    double p0, dp;
+};
+__host__ __device__ inline FanRay fan_ray(double cb, double sb, double R, double inv_ds, double half, double g) {
+    const double inv = 1.0 / (-R * sb * inv_ds - g * cb);
+    const double El = R * cb * inv_ds - g * sb;
+    FanRay r;
+    r.dp = -El * inv;
+    r.p0 = half - g * R * inv - r.dp * half;
+    return r;
+}
+__host__ __device__ inline void turn_by(int q, double& c, double& s) {   // q quarter turns, exactly
+    const double x = c, y = s;
+    if (q == 1) { c = -y; s = x; }
+    else if (q == 2) { c = -x; s = -y; }
+    else if (q == 3) { c = y; s = -x; }
+}
+// Quarter turns that bring the ray of view (cb, sb) to bin offset g nearest to +y.
+__host__ __device__ inline int fan_turns(double cb, double sb, double R, double ds, double g) {
+    const double dx = g * ds * sb - R * cb, dy = -g * ds * cb - R * sb;
+    if (fabs(dy) >= fabs(dx)) return dy > 0.0 ? 0 : 2;
+    return dx > 0.0 ? 1 : 3;
+}
+// What the rows r0 .. r1 ask of a window: the first taps of the bins j0 .. j0 + 15 of one
+// view lie in (lo, hi], and no bin has more than ceil(width) pixels (crossings are monotone
+// and their differences monotone in the bin, both affine in the row: extremes at the corners).
+struct FanEdges {
+    FanRay a, b, c, d;                              // rays j0 - 1, j0 + 1, j0 + 14, j0 + 16
+};
+struct FanReach {
+    double lo, hi, width;
+};
+__host__ __device__ inline FanEdges fan_edges(double cb, double sb, double R, double inv_ds, double half, double g0) {
+    FanEdges e;
+    e.a = fan_ray(cb, sb, R, inv_ds, half, g0 + 1.0);
+    e.b = fan_ray(cb, sb, R, inv_ds, half, g0 - 1.0);
+    e.c = fan_ray(cb, sb, R, inv_ds, half, g0 - (kProjBins - 2));
+    e.d = fan_ray(cb, sb, R, inv_ds, half, g0 - kProjBins);
+    return e;
+}
+__host__ __device__ inline FanReach fan_reach(const FanEdges& e, double r0, double r1) {
+    const double a0 = e.a.p0 + r0 * e.a.dp, a1 = e.a.p0 + r1 * e.a.dp, c0 = e.c.p0 + r0 * e.c.dp, c1 = e.c.p0 + r1 * e.c.dp;
+    FanReach f;
+    f.lo = fmin(fmin(a0, a1), fmin(c0, c1));
+    f.hi = fmax(fmax(a0, a1), fmax(c0, c1));
+    f.width = fmax(fmax(fabs(e.b.p0 + r0 * e.b.dp - a0), fabs(e.b.p0 + r1 * e.b.dp - a1)),
+                   fmax(fabs(e.d.p0 + r0 * e.d.dp - c0), fabs(e.d.p0 + r1 * e.d.dp - c1)));
+    return f;
+}
+
+// Geometry of the turned images of one slice: `rows` rows of `pitch` pixels, pixel p at
+// kFanBorder + p; M = 4: one float4 per pixel, M = 1: four planes of floats.
+__host__ __device__ inline int fan_pitch(int N) { return N + 2 * kFanBorder; }
+__host__ __device__ inline int fan_rows(int N) { return (N + kFanLines - 1) / kFanLines * kFanLines; }
+
+template <int M>
+struct FanCell {
+    using type = float __attribute__((ext_vector_type(4)));
+};
+template <>
+struct FanCell<1> {
+    using type = float;
+};
+
+// M turned images, S slices, A views per workgroup (P waves per view take the rows of a
+// chunk between them).
+template <int M, int S, int A>
+__global__ __launch_bounds__(A == 8 ? 512 : 128 * A, A >= 4 ? 4 : 1) void fan_staged_kernel(FanStagedJob job) {
+    using C = typename FanCell<M>::type;
+    constexpr int P = A == 8 ? 1 : 2;
+    constexpr int W = A * P, kThreads = 64 * W;
+    constexpr int NS = 2 / P;                       // steps of this wave (four rows each)
+    constexpr int RW = kFanLines / W;               // rows staged per wave
+    __shared__ __attribute__((aligned(16))) C win[2][S][kFanLines][kFanCells];
+    extern __shared__ int fan_lds[];                // [chunks]{first pixel, last first tap, taps}, [A][chunks] own origins
+    const int N = job.N, D = job.D;
+    const int nch = (N + kFanLines - 1) / kFanLines;
+    int* own_lds = fan_lds + 3 * nch;
+    const int per_slice = job.groups * job.bin_blocks;
+    int b = blockIdx.x;
+    if (job.stratum > 0) {                          // balanced order (see project_staged_kernel)
+        const int q = b / job.stratum;
+        if ((q & 1) && (q + 1) * job.stratum <= (int)gridDim.x) b = (2 * q + 1) * job.stratum - 1 - b;
+    } else {
+        b = xcd_logical(b, gridDim.x);
+    }
+    const int s0 = (b / per_slice) * S;
+    const int rest = b % per_slice;
+    // bin blocks from the middle of the detector outwards: the longest walks first
+    const int out = rest / job.groups, mid = (job.bin_blocks - 1) >> 1;
+    const int jb = (out & 1) ? mid + ((out + 1) >> 1) : mid - (out >> 1);
+    const int first = (rest - out * job.groups) * A;
+    const int n_ang = min(A, job.n_base - first);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const double half = job.half_pix, R = job.R, inv_ds = job.inv_ds;
+    const int j0 = jb * kBins;
+    const double g0 = job.centre_det - (double)j0;
+    // the turn of the walks: by the middle bin's ray of the middle view of the largest
+    // group, so that smaller groups walk the same rows
+    const int set = first / job.most * job.most;
+    const ProjAngle* em = job.tab + set + (min(job.most, job.n_base - set) >> 1);
+    const int turn = __builtin_amdgcn_readfirstlane(fan_turns(em->a, em->b, R, 1.0 / inv_ds, g0 - 0.5 * (kBins - 1)));
+
+    for (int c = tid; c < nch; c += kThreads) {
+        fan_lds[3 * c] = INT32_MAX;
+        fan_lds[3 * c + 1] = INT32_MIN;
+        fan_lds[3 * c + 2] = 1;
+    }
+    __syncthreads();
+    for (int i = tid / (kThreads / A); i < n_ang; i += A) {
+        double cb = job.tab[first + i].a, sb = job.tab[first + i].b;
+        turn_by(turn, cb, sb);
+        const FanEdges ed = fan_edges(cb, sb, R, inv_ds, half, g0);
+        for (int c = tid % (kThreads / A); c < nch; c += kThreads / A) {
+            const FanReach f = fan_reach(ed, (double)(c * kFanLines), (double)(c * kFanLines + kFanLines - 1));
+            const int lo = (int)floor(f.lo) - 1;
+            own_lds[i * nch + c] = lo;
+            atomicMin(&fan_lds[3 * c], lo);
+            atomicMax(&fan_lds[3 * c + 1], (int)floor(f.hi));
+            atomicMax(&fan_lds[3 * c + 2], min(kFanTaps, (int)ceil(f.width)));
+        }
+    }
+
+    // this wave's view, and this lane's bin and rows
+    const int ia = wave & (A - 1), part = wave / A;
+    const bool active = ia < n_ang;
+    const ProjAngle* e = job.tab + first + (active ? ia : 0);
+    double cb = e->a, sb = e->b;
+    turn_by(turn, cb, sb);
+    const int li = lane / kBins;
+    const double g = g0 - (double)(lane & (kBins - 1));
+    const FanRay below = fan_ray(cb, sb, R, inv_ds, half, g + 1.0), ray = fan_ray(cb, sb, R, inv_ds, half, g);
+    const float gap0 = (float)(ray.p0 - below.p0), dgap = (float)(ray.dp - below.dp);    // ray j - ray j-1, row 0 and per row
+    const double inv_R = 1.0 / R;
+    // depth / R along ray j: L = R - x cb - y sb with x = p - half, y = l - half
+    const float dep0 = (float)(1.0 - ((ray.p0 - half) * cb - half * sb) * inv_R), ddep = (float)(-(ray.dp * cb + sb) * inv_R);
+    const float lq = (float)(-cb * inv_R), eq = (float)((-R * sb * inv_ds - g * cb) * inv_R);
+    const float min_dep = (float)(kFanMinDepth * inv_R);
+    float step[NS];                                 // first-tap position from row li of a chunk to the row of step q
+#pragma unroll
+    for (int q = 0; q < NS; ++q) step[q] = (float)((double)(4 * (part + P * q)) * below.dp);
+
+    const int pitch = fan_pitch(N);
+    const size_t plane = (size_t)fan_rows(N) * pitch;      // pixels
+    // M = 1: the turned image the walk reads
+    const C* __restrict__ turned = reinterpret_cast<const C*>(job.turned) + (M == 1 ? (size_t)((4 - turn) & 3) * plane : 0);
+    const C* src[S];
+#pragma unroll
+    for (int z = 0; z < S; ++z) src[z] = turned + (size_t)min(s0 + z, job.n_slices - 1) * plane * (4 / M) + kFanBorder;
+    C pf[S][RW], px[S] = {};                        // px: cells 64 .. 95 of two rows per wave, of wide windows only
+    const int xrow = wave * 2 + (lane >> 5), xcol = 64 + (lane & 31);
+    auto wide = [&](const int2& w) { return w.y - w.x > 64; };
+    auto load = [&](int c, const int2& w) {
+        const int base = c * kFanLines * pitch + w.x, col = min(lane, w.y - w.x - 1);   // nothing past the window
+#pragma unroll
+        for (int z = 0; z < S; ++z)
+#pragma unroll
+            for (int h = 0; h < RW; ++h) pf[z][h] = src[z][base + (wave * RW + h) * pitch + col];
+        if (W >= 4 && wide(w) && xrow < kFanLines)
+#pragma unroll
+            for (int z = 0; z < S; ++z) px[z] = src[z][base + xrow * pitch + xcol];
+    };
+    auto store = [&](int buf, int c, const int2& w) {
+#pragma unroll
+        for (int z = 0; z < S; ++z)
+#pragma unroll
+            for (int h = 0; h < RW; ++h) win[buf][z][wave * RW + h][lane] = pf[z][h];
+        if (wide(w)) {
+            if constexpr (W >= 4) {
+                if (xrow < kFanLines)
+#pragma unroll
+                    for (int z = 0; z < S; ++z) win[buf][z][xrow][xcol] = px[z];
+            } else {                                // few waves: the wide windows' cells as they come
+                for (int o = tid; o < kFanLines * 32; o += kThreads)
+#pragma unroll
+                    for (int z = 0; z < S; ++z)
+                        win[buf][z][o >> 5][64 + (o & 31)] = src[z][(c * kFanLines + (o >> 5)) * pitch + w.x + 64 + (o & 31)];
+            }
+        }
+    };
+    float acc[NS][S][M];
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int z = 0; z < S; ++z)
+#pragma unroll
+            for (int m = 0; m < M; ++m) acc[q][z][m] = 0.0f;
+    auto next = [&](int c, int2& w, int& taps) {    // the next chunk whose window meets the image
+        for (++c; c < nch; ++c) {
+            taps = __builtin_amdgcn_readfirstlane(fan_lds[3 * c + 2]);
+            w.x = __builtin_amdgcn_readfirstlane(fan_lds[3 * c]);
+            w.y = __builtin_amdgcn_readfirstlane(fan_lds[3 * c + 1]) + taps + 2;
+            if (w.x < N && w.y > 0) break;
+        }
+        return c;
+    };
+    auto compute = [&](auto taps, int buf, int c, int wlo) {
+        constexpr int T = decltype(taps)::value;
+        const int own = own_lds[(active ? ia : 0) * nch + c];
+        const int l0 = c * kFanLines + li;
+        const float xr = (float)(fma((double)l0, below.dp, below.p0) - (double)own);
+        const C* __restrict__ row0 = &win[buf][0][li + 4 * part][0] + (own - wlo);
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const float x = xr + step[q];           // >= 1 up to rounding: truncation is floor
+            const int i = (int)x;
+            const float f = __builtin_amdgcn_fractf(x);
+            const C* __restrict__ at = row0 + 4 * P * q * kFanCells + i;
+            const float fl = (float)(l0 + 4 * (part + P * q));
+            const float d0 = (1.0f - f) - fmaf(fl, dgap, gap0);       // first tap - ray j
+            const float dep = fmaxf(fmaf(fl, ddep, dep0), min_dep);
+#pragma unroll
+            for (int m = 0; m < T; ++m) {
+                const float d = d0 + (float)m;
+                const float inv = __builtin_amdgcn_rcpf(fmaf(lq, d, dep));            // R / L
+                const float h = __builtin_amdgcn_fmed3f(1.0f - fabsf(d) * (eq * inv), 0.0f, 1.0f);
+                const float w = h * inv * inv;
+#pragma unroll
+                for (int z = 0; z < S; ++z) {
+                    const C v = at[z * kFanLines * kFanCells + m + 1];
+                    if constexpr (M == 1) {
+                        acc[q][z][0] = fmaf(w, v, acc[q][z][0]);
+                    } else {
+#pragma unroll
+                        for (int y = 0; y < M; ++y) acc[q][z][y] = fmaf(w, v[y], acc[q][z][y]);
+                    }
+                }
+            }
+        }
+    };
+    __syncthreads();                                // windows made
+    int2 w0 = make_int2(0, 0), w1 = w0;
+    int t0 = 1, t1 = 1;
+    int c = next(-1, w0, t0);
+    if (c < nch) load(c, w0);
+    for (int buf = 0; c < nch; buf ^= 1) {
+        store(buf, c, w0);
+        const int cn = next(c, w1, t1);
+        if (cn < nch) load(cn, w1);
+        __syncthreads();                            // one per chunk, as in project_staged_kernel
+        if (active) {
+            switch (t0) {
+                case 1: compute(std::integral_constant<int, 1>{}, buf, c, w0.x); break;
+                case 2: compute(std::integral_constant<int, 2>{}, buf, c, w0.x); break;
+                case 3: compute(std::integral_constant<int, 3>{}, buf, c, w0.x); break;
+                case 4: compute(std::integral_constant<int, 4>{}, buf, c, w0.x); break;
+                case 5: compute(std::integral_constant<int, 5>{}, buf, c, w0.x); break;
+                default: compute(std::integral_constant<int, kFanTaps>{}, buf, c, w0.x); break;
+            }
+        }
+        c = cn;
+        w0 = w1;
+        t0 = t1;
+    }
+
+    // the eight sums of each bin, in step and row order
+    __syncthreads();
+    constexpr int V = S * M;
+    float* part_lds = reinterpret_cast<float*>(&win[0][0][0][0]);   // [A][2][V][64]
+    static_assert(sizeof(float) * A * 2 * V * 64 <= sizeof(win), "sums fit the windows");
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int z = 0; z < S; ++z)
+#pragma unroll
+            for (int m = 0; m < M; ++m) part_lds[((ia * 2 + part + P * q) * V + z * M + m) * 64 + lane] = acc[q][z][m];
+    __syncthreads();
+    for (int o = tid; o < n_ang * V * kBins; o += kThreads) {
+        const int bin = o & (kBins - 1), v = (o / kBins) % V, i = o / (kBins * V);
+        float sum = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int z = 0; z < 64 / kBins; ++z) sum += part_lds[((i * 2 + q) * V + v) * 64 + z * kBins + bin];
+        const ProjAngle* ea = job.tab + first + i;
+        const int k = M == 4 ? ea->k0 + ((turn - ea->t + v % M) & 3) * (job.K >> 2) : ea->k0;
+        const int s = s0 + v / M, j = j0 + bin;
+        if (j < D && s < job.n_slices) job.sino[((size_t)s * job.K + k) * D + j] = sum * job.scale;
+    }
+}
+
+// The turned images of n slices for fan_staged_kernel (fan_pitch, fan_rows), zeros around
+// them: I_0[l][p] = img[l][p], I_1[l][p] = img[p][N-1-l], I_2[l][p] = img[N-1-l][N-1-p],
+// I_3[l][p] = img[N-1-p][l].  Tiles of 32 x 32 pixels, I_1 and I_3 transposed through LDS.
+constexpr int kTurnTile = 32;
+template <int M>
+__global__ __launch_bounds__(256) void turn_kernel(const float* __restrict__ img, float* __restrict__ turned, int N,
+                                                   int tiles_l, int tiles_p) {
+    __shared__ float t1[kTurnTile][kTurnTile + 1], t3[kTurnTile][kTurnTile + 1];
+    const int per = tiles_l * tiles_p;
+    const int s = blockIdx.x / per, t = blockIdx.x - s * per;
+    const int l0 = (t / tiles_p) * kTurnTile, p0 = (t % tiles_p) * kTurnTile - kFanBorder;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int pitch = fan_pitch(N), rows = fan_rows(N);
+    const float* __restrict__ src = img + (size_t)s * N * N;
+#pragma unroll
+    for (int i = 0; i < kTurnTile; i += 8) {
+        const int p = p0 + ty + i, l = l0 + tx;
+        const bool in = (unsigned)p < (unsigned)N && l < N;
+        t1[ty + i][tx] = in ? src[(size_t)p * N + (N - 1 - l)] : 0.0f;
+        t3[ty + i][tx] = in ? src[(size_t)(N - 1 - p) * N + l] : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kTurnTile; i += 8) {
+        const int l = l0 + ty + i, p = p0 + tx;
+        if (l >= rows || p + kFanBorder >= pitch) continue;
+        const bool in = (unsigned)p < (unsigned)N && l < N;
+        const float v0 = in ? src[(size_t)l * N + p] : 0.0f, v2 = in ? src[(size_t)(N - 1 - l) * N + (N - 1 - p)] : 0.0f;
+        const float v1 = t1[tx][ty + i], v3 = t3[tx][ty + i];
+        const size_t plane = (size_t)rows * pitch, at = (size_t)l * pitch + (p + kFanBorder);
+        if constexpr (M == 4) {
+            reinterpret_cast<float4*>(turned)[(size_t)s * plane + at] = make_float4(v0, v1, v2, v3);
+        } else {
+            float* dst = turned + (size_t)s * 4 * plane + at;
+            dst[0] = v0;
+            dst[plane] = v1;
+            dst[2 * plane] = v2;
+            dst[3 * plane] = v3;
         }
     }
 }
@@ -610,6 +973,108 @@ hipError_t launch_project_staged(ProjStagedJob job, int M, int A_max, int T, boo
     const dim3 grid((unsigned)blocks);
     return M == 4 ? launch_staged_taps<4>(job, A, T, fast3, grid, lds, stream)
                   : launch_staged_taps<2>(job, A, T, fast3, grid, lds, stream);
+}
+
+// Views per workgroup of the staged fan projector, the largest power of two whose windows
+// fit for every group and bin block; 0: none does, or a bin has more than kFanTaps pixels
+// on a row, or rays run too far from the columns, or the source is too close to the image
+// for the depth clamp.  A window's width is convex in the row, so the first and the last
+// chunk that meet the image bound every chunk between them.
+int fan_group_views(const std::vector<ProjAngle>& tab, int N, int D, double R, double ds) {
+    const double half = 0.5 * (N - 1), cd = 0.5 * (D - 1), inv_ds = 1.0 / ds;
+    if (N > 4096 || !(R - 0.70710678118654752 * N >= kFanMinDepth + kFanTaps + 2.0)) return 0;
+    const int n = (int)tab.size(), nch = (N + kFanLines - 1) / kFanLines;
+    auto group_fits = [&](int i0, int na, int j0) {
+        const double g0 = cd - j0;
+        const ProjAngle& em = tab[(size_t)i0 + (na >> 1)];
+        const int q = fan_turns(em.a, em.b, R, ds, g0 - 0.5 * (kProjBins - 1));
+        FanEdges ed[kProjWaves];
+        for (int i = 0; i < na; ++i) {
+            double c = tab[(size_t)i0 + i].a, s = tab[(size_t)i0 + i].b;
+            turn_by(q, c, s);
+            for (double g : {g0 + 1.0, g0 - kProjBins}) {              // rays stay within 60 degrees of the columns
+                const double dx = g * ds * s - R * c, dy = -g * ds * c - R * s;
+                if (!(dy >= 0.5 * std::hypot(dx, dy))) return false;
+            }
+            ed[i] = fan_edges(c, s, R, inv_ds, half, g0);
+        }
+        // 0: no pixel of the image, 1: fits, -1: does not
+        auto chunk = [&](int c) {
+            double lo = INFINITY, hi = -INFINITY, width = 0.0;
+            for (int i = 0; i < na; ++i) {
+                const FanReach f = fan_reach(ed[i], (double)(c * kFanLines), (double)(c * kFanLines + kFanLines - 1));
+                lo = std::min(lo, f.lo);
+                hi = std::max(hi, f.hi);
+                width = std::max(width, f.width);
+            }
+            const double taps = std::ceil(width);
+            if (lo - 2.0 > (double)N || hi + taps + 3.0 < 0.0) return 0;
+            return width <= kFanTaps - 0.01 && hi - lo + taps + 4.5 <= (double)kFanCells ? 1 : -1;
+        };
+        for (int c = 0; c < nch; ++c)
+            if (const int f = chunk(c)) {
+                if (f < 0) return false;
+                break;
+            }
+        for (int c = nch - 1; c >= 0; --c)
+            if (const int f = chunk(c)) return f > 0;
+        return true;
+    };
+    for (int A = kProjWaves; A >= 1; A >>= 1) {
+        bool fits = true;
+        for (int i0 = 0; i0 < n && fits; i0 += A)
+            for (int j0 = 0; j0 < D && fits; j0 += kProjBins) fits = group_fits(i0, std::min(A, n - i0), j0);
+        if (fits) return A;
+    }
+    return 0;
+}
+
+size_t fan_turned_floats(int N) { return (size_t)4 * fan_rows(N) * fan_pitch(N); }
+
+hipError_t launch_turn(const float* img, float* turned, int N, int M, int n_slices, hipStream_t stream) {
+    if (n_slices <= 0) return hipSuccess;
+    const int tiles_l = (fan_rows(N) + kTurnTile - 1) / kTurnTile, tiles_p = (fan_pitch(N) + kTurnTile - 1) / kTurnTile;
+    const int64_t blocks = (int64_t)tiles_l * tiles_p * n_slices;
+    if (blocks > INT32_MAX || (M != 1 && M != 4)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(256);
+    return M == 4 ? launch_kernel(turn_kernel<4>, grid, block, 0, stream, img, turned, N, tiles_l, tiles_p)
+                  : launch_kernel(turn_kernel<1>, grid, block, 0, stream, img, turned, N, tiles_l, tiles_p);
+}
+
+template <int M, int S>
+hipError_t launch_fan_views(const FanStagedJob& job, int A, dim3 grid, size_t lds, hipStream_t stream) {
+    switch (A) {
+        case 8: return launch_kernel(fan_staged_kernel<M, S, 8>, grid, dim3(512), lds, stream, job);
+        case 4: return launch_kernel(fan_staged_kernel<M, S, 4>, grid, dim3(512), lds, stream, job);
+        case 2: return launch_kernel(fan_staged_kernel<M, S, 2>, grid, dim3(256), lds, stream, job);
+        default: return launch_kernel(fan_staged_kernel<M, S, 1>, grid, dim3(128), lds, stream, job);
+    }
+}
+
+hipError_t launch_fan_project_staged(FanStagedJob job, int M, int A_max, int n_slices, hipStream_t stream) {
+    if (n_slices <= 0) return hipSuccess;
+    if (A_max < 1 || A_max > kProjWaves || (A_max & (A_max - 1)) || (M != 1 && M != 4) || (M == 4 && job.K % 4 != 0))
+        return hipErrorInvalidValue;
+    job.n_slices = n_slices;
+    job.most = A_max;
+    job.bin_blocks = (job.D + kBins - 1) / kBins;
+    // slices that share positions and weights
+    const int S = n_slices == 1 ? 1 : M == 4 ? 2 : 4;
+    const int sets = (n_slices + S - 1) / S;
+    int A = A_max;
+    auto blocks_of = [&](int a) {
+        job.groups = (job.n_base + a - 1) / a;
+        return (int64_t)job.groups * job.bin_blocks * sets;
+    };
+    while (A > 2 && blocks_of(A) < 2 * (int64_t)current_device_cus()) A >>= 1;
+    const int64_t blocks = blocks_of(A);
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    job.stratum = sets < 8 ? current_device_cus() : 0;
+    const size_t lds = sizeof(int) * (3 + A) * (size_t)((job.N + kFanLines - 1) / kFanLines);
+    const dim3 grid((unsigned)blocks);
+    if (M == 4)
+        return S == 1 ? launch_fan_views<4, 1>(job, A, grid, lds, stream) : launch_fan_views<4, 2>(job, A, grid, lds, stream);
+    return S == 1 ? launch_fan_views<1, 1>(job, A, grid, lds, stream) : launch_fan_views<1, 4>(job, A, grid, lds, stream);
 }
 
 hipError_t launch_transpose(const float* img, float* out, int N, int n_slices, hipStream_t stream) {

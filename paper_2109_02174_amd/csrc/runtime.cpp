@@ -15,6 +15,7 @@
 #include <sstream>
 #include <string>
 #include <tuple>
+#include <utility>
 #include <vector>
 
 #include "../../include/fbp.h"
@@ -653,6 +654,43 @@ ProjLayout parallel_project_layout(const Plan& p, std::vector<ProjAngle>* tab) {
     } else {
         tab->clear();
         L.slice_floats = (size_t)2 * (size_t)(p.N + 1) * (size_t)L.pitch;
+    }
+    return L;
+}
+
+// Kernel and scratch layout of a fan-beam projector: the staged one where its windows
+// fit, else padded copies.  Base views: for quarter-turn lists the first K/4 turned back
+// into [0, pi/2), else every view; sorted by angle.
+ProjLayout fan_projector_layout(const Plan& p, std::vector<ProjAngle>* tab) {
+    ProjLayout L = fan_project_layout(p);
+    if (L.T == 0) return L;
+    const bool quarter = fan_quarter_turns(p.angles);
+    const int n = quarter ? p.K / 4 : p.K;
+    std::vector<std::pair<double, ProjAngle>> views((size_t)n);
+    for (int k = 0; k < n; ++k) {
+        double c = std::cos(p.angles[k]), s = std::sin(p.angles[k]);
+        ProjAngle e{};
+        e.k0 = e.k1 = k;
+        while (quarter && !(c > 0.0 && s >= 0.0) && e.t < 4) {     // back by a quarter turn
+            const double x = c;
+            c = s;
+            s = -x;
+            ++e.t;
+        }
+        e.t &= 3;
+        e.a = c;
+        e.b = s;
+        views[(size_t)k] = {std::atan2(s, c), e};
+    }
+    std::stable_sort(views.begin(), views.end(), [](const auto& x, const auto& y) { return x.first < y.first; });
+    tab->clear();
+    for (const auto& v : views) tab->push_back(v.second);
+    L.A = fan_group_views(*tab, p.N, p.D, p.R, p.dt);
+    if (L.A > 0) {
+        L.M = quarter ? 4 : 1;
+        L.slice_floats = fan_turned_floats(p.N);
+    } else {
+        tab->clear();
     }
     return L;
 }
@@ -2154,7 +2192,7 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
     std::lock_guard<std::mutex> lock(ps.mu);
     if (!ps.ptr) {
         std::vector<ProjAngle> tab;
-        ps.layout = fan ? fan_project_layout(*p) : parallel_project_layout(*p, &tab);
+        ps.layout = fan ? fan_projector_layout(*p, &tab) : parallel_project_layout(*p, &tab);
         if (ps.layout.T == 0) return FBP_EUNSUPPORTED;
         const size_t slice_bytes = sizeof(float) * ps.layout.slice_floats;
         const int slices = (int)std::max<size_t>(1, std::min<size_t>(16, ((size_t)256 << 20) / slice_bytes));
@@ -2180,7 +2218,20 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
     ProjJob j{};
     ProjStagedJob sj{};
     FanProjJob fj{};
-    if (fan) {
+    FanStagedJob fs{};
+    if (fan && L.A > 0) {
+        fs.turned = ps.ptr;
+        fs.tab = ps.d_tab;
+        fs.R = p->R;
+        fs.inv_ds = 1.0 / p->dt;
+        fs.half_pix = 0.5 * (double)(p->N - 1);
+        fs.centre_det = 0.5 * (double)(p->D - 1);
+        fs.N = p->N;
+        fs.K = p->K;
+        fs.D = p->D;
+        fs.n_base = ps.n_base;
+        fs.scale = (float)(2.0 * kPi / (double)p->K);
+    } else if (fan) {
         fj.pimg = ps.ptr;
         fj.cs = p->d_fcs;
         fj.R = p->R;
@@ -2225,10 +2276,14 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
     for (int32_t i0 = 0; i0 < n_slices; i0 += ps.slices) {
         const int n = std::min<int32_t>(ps.slices, n_slices - i0);
         const float* src = d_image + (size_t)i0 * is;
-        hipError_t e = L.A > 0 ? launch_transpose(src, ps.ptr, p->N, n, s)
-                               : launch_pad(src, ps.ptr, p->N, L.pad, L.pitch, n, s);
+        hipError_t e = L.A == 0 ? launch_pad(src, ps.ptr, p->N, L.pad, L.pitch, n, s)
+                       : fan    ? launch_turn(src, ps.ptr, p->N, L.M, n, s)
+                                : launch_transpose(src, ps.ptr, p->N, n, s);
         if (e == hipSuccess) {
-            if (fan) {
+            if (fan && L.A > 0) {
+                fs.sino = d_sino + (size_t)i0 * qs;
+                e = launch_fan_project_staged(fs, L.M, L.A, n, s);
+            } else if (fan) {
                 fj.sino = d_sino + (size_t)i0 * qs;
                 e = launch_fan_project(fj, n, s);
             } else if (L.A > 0) {
