@@ -408,7 +408,7 @@ __global__ __launch_bounds__(A == 8 ? 512 : 128 * A, A >= 4 ? 4 : 1) void fan_st
     constexpr int NS = 2 / P;                       // steps of this wave (four rows each)
     constexpr int RW = kFanLines / W;               // rows staged per wave
     __shared__ __attribute__((aligned(16))) C win[2][S][kFanLines][kFanCells];
-    extern __shared__ int fan_lds[];                // [chunks]{first pixel, last first tap, taps}, [A][chunks] own origins
+    extern __shared__ int fan_lds[];                // [chunks]{first pixel, end, taps}, [A][chunks] own origins, own ends
     const int N = job.N, D = job.D;
     const int nch = (N + kFanLines - 1) / kFanLines;
     int* own_lds = fan_lds + 3 * nch;
@@ -438,24 +438,29 @@ __global__ __launch_bounds__(A == 8 ? 512 : 128 * A, A >= 4 ? 4 : 1) void fan_st
     const ProjAngle* em = job.tab + set + (min(job.most, job.n_base - set) >> 1);
     const int turn = __builtin_amdgcn_readfirstlane(fan_turns(em->a, em->b, R, 1.0 / inv_ds, g0 - 0.5 * (kBins - 1)));
 
-    for (int c = tid; c < nch; c += kThreads) {
-        fan_lds[3 * c] = INT32_MAX;
-        fan_lds[3 * c + 1] = INT32_MIN;
-        fan_lds[3 * c + 2] = 1;
-    }
-    __syncthreads();
+    // per view and chunk, then per chunk over the views: the window and its tap count
+    int* end_lds = own_lds + A * nch;               // 8 * (last first tap) + taps
     for (int i = tid / (kThreads / A); i < n_ang; i += A) {
         double cb = job.tab[first + i].a, sb = job.tab[first + i].b;
         turn_by(turn, cb, sb);
         const FanEdges ed = fan_edges(cb, sb, R, inv_ds, half, g0);
         for (int c = tid % (kThreads / A); c < nch; c += kThreads / A) {
             const FanReach f = fan_reach(ed, (double)(c * kFanLines), (double)(c * kFanLines + kFanLines - 1));
-            const int lo = (int)floor(f.lo) - 1;
-            own_lds[i * nch + c] = lo;
-            atomicMin(&fan_lds[3 * c], lo);
-            atomicMax(&fan_lds[3 * c + 1], (int)floor(f.hi));
-            atomicMax(&fan_lds[3 * c + 2], min(kFanTaps, (int)ceil(f.width)));
+            own_lds[i * nch + c] = (int)floor(f.lo) - 1;
+            end_lds[i * nch + c] = (int)floor(f.hi) * 8 + max(1, min(kFanTaps, (int)ceil(f.width)));
         }
+    }
+    __syncthreads();
+    for (int c = tid; c < nch; c += kThreads) {
+        int lo = INT32_MAX, hi = INT32_MIN, taps = 1;
+        for (int i = 0; i < n_ang; ++i) {
+            lo = min(lo, own_lds[i * nch + c]);
+            hi = max(hi, end_lds[i * nch + c] >> 3);
+            taps = max(taps, end_lds[i * nch + c] & 7);
+        }
+        fan_lds[3 * c] = lo;
+        fan_lds[3 * c + 1] = hi + taps + 2;
+        fan_lds[3 * c + 2] = taps;
     }
 
     // this wave's view, and this lane's bin and rows
@@ -526,7 +531,7 @@ __global__ __launch_bounds__(A == 8 ? 512 : 128 * A, A >= 4 ? 4 : 1) void fan_st
         for (++c; c < nch; ++c) {
             taps = __builtin_amdgcn_readfirstlane(fan_lds[3 * c + 2]);
             w.x = __builtin_amdgcn_readfirstlane(fan_lds[3 * c]);
-            w.y = __builtin_amdgcn_readfirstlane(fan_lds[3 * c + 1]) + taps + 2;
+            w.y = __builtin_amdgcn_readfirstlane(fan_lds[3 * c + 1]);
             if (w.x < N && w.y > 0) break;
         }
         return c;
@@ -1070,7 +1075,7 @@ hipError_t launch_fan_project_staged(FanStagedJob job, int M, int A_max, int n_s
     const int64_t blocks = blocks_of(A);
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     job.stratum = sets < 8 ? current_device_cus() : 0;
-    const size_t lds = sizeof(int) * (3 + A) * (size_t)((job.N + kFanLines - 1) / kFanLines);
+    const size_t lds = sizeof(int) * (3 + 2 * A) * (size_t)((job.N + kFanLines - 1) / kFanLines);
     const dim3 grid((unsigned)blocks);
     if (M == 4)
         return S == 1 ? launch_fan_views<4, 1>(job, A, grid, lds, stream) : launch_fan_views<4, 2>(job, A, grid, lds, stream);
