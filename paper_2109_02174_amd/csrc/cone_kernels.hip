@@ -275,6 +275,285 @@ __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
     }
 }
 
+// ---------------------------------------------------------------- quarter-turn form
+//
+// View lists closed under quarter turns (K = 4 K4, view k + j K4 at angle b_k + j pi/2).
+// Turning a column by a quarter turn and the view with it leaves (u, v, rho) unchanged,
+// so column R^t p at a base view k < K4 sees the detector where column R^(t+j) p sees it
+// at view k + j K4: one set of coordinates and bilinear weights serves four samples.
+//  * A workgroup owns a 16 x 16 tile of the base region (rows [0, N/2), columns
+//    [0, (N+1)/2): for odd N a pinwheel piece, the centre column apart) and its three
+//    turns, kConeRotZB slices deep; a lane holds 4 kConeRotZB voxels.
+//  * An item is (base view k, turn t): the tile's window at view b_k turned back by t, of
+//    the views k + j K4, j = 0..3, staged as cells of four values, so that the four
+//    corners of a sample are four 16-byte LDS reads for four voxels.
+//  * The next item's cells load into registers while the current one is summed; items are
+//    summed in a fixed order, each voxel is written once, no atomics.
+// Bound by VALU issue (256^3, 360 views, 256 x 384 detector: 0.71 G wave instructions, 7.5
+// a sample against 13.3 of one column per lane, 1.16 ms at full issue; LDS 1.1 ms), with
+// four waves a SIMD.  Measured there, filter included: 1.72 ms against 2.54 ms.  Three
+// waves a SIMD without spills: 2.14 ms; 12 slices a workgroup 2.00 ms; one end of the
+// window area for every item (two barriers an item): 1.86 ms.
+constexpr int kConeRotItems = 32;                       // items whose windows are made at once
+constexpr int kConeRotRegs = 3;                         // cells a thread prefetches (the rest, of the largest windows, load late)
+constexpr int kConeRotInts = 16;                        // per-item words in LDS
+
+__global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) {
+    extern __shared__ __align__(16) char smem[];
+    const int N = job.N, K4 = job.K >> 2, Du = job.Du, Dv = job.Dv;
+    // per item: n0 n1 n2 cvj | d0 d1 d2 umax | vmax (floats), column origin, row origin, columns, rows (ints)
+    float* coef = reinterpret_cast<float*>(smem);
+    float4* win = reinterpret_cast<float4*>(coef + kConeRotInts * kConeRotItems);
+    const int tiles_y = ((N >> 1) + kConeTile - 1) / kConeTile;
+    const int tiles = job.tiles_x * tiles_y;
+    const int zb = blockIdx.x / tiles;
+    const int tile = blockIdx.x - zb * tiles;
+    const int c0 = (tile % job.tiles_x) * kConeTile, r0 = (tile / job.tiles_x) * kConeTile;
+    const int z0 = zb * kConeRotZB;
+    const int zn = min(kConeRotZB, job.Nz - z0);
+    const int tid = threadIdx.x;
+    const int dx = tid & (kConeTile - 1), dy = tid / kConeTile;
+    const int nbx = (N + 1) >> 1, nby = N >> 1;          // base region
+    const int cw = min(kConeTile, nbx - c0), rh = min(kConeTile, nby - r0);
+    const float fdx = (float)dx, fdy = (float)dy;
+    const double zlo = (double)z0 - job.half_z, zhi = zlo + (double)(zn - 1);
+    const float zlo_dv = (float)(zlo / job.dv), inv_dv = (float)(1.0 / job.dv);
+    const int items = 4 * K4;
+    const size_t view = (size_t)Dv * Du;
+
+    float acc[4][kConeRotZB];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int q = 0; q < kConeRotZB; ++q) acc[m][q] = 0.0f;
+
+    // windows of the items i0 .. i0 + kConeRotItems - 1 (see cone_bp_kernel), one per lane of wave 0
+    auto windows = [&](int i0) {
+        const int it = i0 + tid;
+        if (tid < kConeRotItems && it < items) {
+            double c = job.cs[2 * (it >> 2)], sn = job.cs[2 * (it >> 2) + 1];
+            const double cx = c, sx = sn;
+            switch (it & 3) {                            // back by t quarter turns
+                case 1: c = sx; sn = -cx; break;
+                case 2: c = -cx; sn = -sx; break;
+                case 3: c = -sx; sn = cx; break;
+                default: break;
+            }
+            const double R = job.R, du = job.du;
+            const double xt = (double)c0 - job.half_pix, yt = (double)r0 - job.half_pix;
+            const double Lt = R - (c * xt + sn * yt);
+            const double Nt = R * (-sn * xt + c * yt);
+            double Lmin = INFINITY, Lmax = -INFINITY, umin = INFINITY, umax = -INFINITY;
+            for (int q = 0; q < 4; ++q) {
+                const double ex = (q & 1) ? (double)(cw - 1) : 0.0, ey = (q & 2) ? (double)(rh - 1) : 0.0;
+                const double L = Lt - c * ex - sn * ey;
+                const double u = (Nt + R * (-sn * ex + c * ey)) / (L * du);
+                Lmin = fmin(Lmin, L);
+                Lmax = fmax(Lmax, L);
+                umin = fmin(umin, u);
+                umax = fmax(umax, u);
+            }
+            const double rlo = R / Lmax, rhi = R / Lmin;
+            const double vmin = fmin(fmin(zlo * rlo, zlo * rhi), fmin(zhi * rlo, zhi * rhi)) / job.dv;
+            const double vmax = fmax(fmax(zlo * rlo, zlo * rhi), fmax(zhi * rlo, zhi * rhi)) / job.dv;
+            const int i0c = (int)floor(umin + job.cu) - 1;
+            const int j0 = (int)floor(vmin + job.cv) - 1;
+            const int nc = min(job.WL + 1, (int)floor(umax + job.cu) + 3 - i0c);
+            const int nr = min(job.WV + 1, (int)floor(vmax + job.cv) + 4 - j0);
+            const double G = ((double)i0c - job.cu) * du;
+            const double a0 = Nt - G * Lt, a1 = -R * sn + G * c, a2 = R * c + G * sn;
+            float* cf = coef + kConeRotInts * tid;
+            cf[0] = (float)(a0 * job.inv_duR);
+            cf[1] = (float)(a1 * job.inv_duR);
+            cf[2] = (float)(a2 * job.inv_duR);
+            cf[3] = (float)(job.cv - (double)j0);
+            cf[4] = (float)(Lt * job.inv_R);
+            cf[5] = (float)(-c * job.inv_R);
+            cf[6] = (float)(-sn * job.inv_R);
+            cf[7] = (float)(nc - 2);
+            cf[8] = (float)(nr - 2);
+            int* og = reinterpret_cast<int*>(cf + 9);
+            og[0] = i0c;
+            og[1] = j0;
+            og[2] = nc;
+            og[3] = nr;
+        }
+    };
+    // one cell of an item: the four views' value at window position e (0 off the detector)
+    struct Window {
+        int i0, j0, nc, cells;
+        float inv_nc;
+    };
+    auto window = [&](int it) {
+        const int* og = reinterpret_cast<const int*>(coef + kConeRotInts * (it & (kConeRotItems - 1)) + 9);
+        Window w;
+        w.i0 = __builtin_amdgcn_readfirstlane(og[0]);
+        w.j0 = __builtin_amdgcn_readfirstlane(og[1]);
+        w.nc = __builtin_amdgcn_readfirstlane(og[2]);
+        w.cells = w.nc * __builtin_amdgcn_readfirstlane(og[3]);
+        w.inv_nc = 1.0f / (float)w.nc;
+        return w;
+    };
+    __amdgpu_buffer_rsrc_t src[4];
+    auto sources = [&](int it) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            src[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(job.q + (size_t)((it >> 2) + j * K4) * view),
+                                                       (short)0, (int)(view * 4), 0x00020000);
+    };
+    auto cell = [&](const Window& w, int e, float (&v)[4]) {
+        // row e / nc, column e % nc (exact, as in cone_stage); past the window's end or off the
+        // detector the offset is past the view, which reads as 0
+        const int rr = (int)(((float)e + 0.5f) * w.inv_nc);
+        const int row = w.j0 + rr, col = w.i0 + e - __mul24(rr, w.nc);
+        const bool in = e < w.cells && (unsigned)row < (unsigned)Dv && (unsigned)col < (unsigned)Du;
+        const int off = in ? (row * Du + col) * 4 : 0x7FFFFFF0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(src[j], off, 0, 0));
+    };
+    float pf[kConeRotRegs][4];
+    Window nxt;
+    auto load = [&](int it) {
+        nxt = window(it);
+        sources(it);
+#pragma unroll
+        for (int i = 0; i < kConeRotRegs; ++i)
+            if (i * kConeThreads < nxt.cells) cell(nxt, tid + i * kConeThreads, pf[i]);
+    };
+    auto store = [&](float4* dst) {
+#pragma unroll
+        for (int i = 0; i < kConeRotRegs; ++i) {
+            const int e = tid + i * kConeThreads;
+            if (e < nxt.cells) dst[e] = make_float4(pf[i][0], pf[i][1], pf[i][2], pf[i][3]);
+        }
+        for (int e = tid + kConeRotRegs * kConeThreads; e < nxt.cells; e += kConeThreads) {
+            float v[4];
+            cell(nxt, e, v);
+            dst[e] = make_float4(v[0], v[1], v[2], v[3]);
+        }
+    };
+    auto compute = [&](auto turn, int it, int pitch, const float4* cells) {
+        constexpr int t = decltype(turn)::value;
+        const float* cf = coef + kConeRotInts * (it & (kConeRotItems - 1));
+        const float4 nf = *reinterpret_cast<const float4*>(cf);
+        const float4 df = *reinterpret_cast<const float4*>(cf + 4);
+        const float vmax = cf[8];
+        const float den = fmaf(df.z, fdy, fmaf(df.y, fdx, df.x));
+        const float num = fmaf(nf.z, fdy, fmaf(nf.y, fdx, nf.x));
+        const float rho = __builtin_amdgcn_rcpf(den);          // R / L
+        const float u = __builtin_amdgcn_fmed3f(num * rho, 0.0f, df.w);
+        const float w = rho * rho;
+        const int iu = (int)u;
+        const float fu = u - (float)iu;
+        const float wb = w * fu, wa = w - wb;                  // column weights
+        const float a = rho * inv_dv;                          // rows per slice
+        const float v0 = fmaf(zlo_dv, rho, nf.w);              // window row of the block's first slice
+        // byte offset of the column in LDS, in one register: a sample's address is one
+        // 24-bit multiply-add
+        unsigned boff = (unsigned)((const char*)(cells + iu) - smem);
+        asm volatile("" : "+v"(boff));
+        const unsigned pitch16 = 16u * (unsigned)pitch;
+        auto sample = [&](int q, float v) {
+            const int iv = (int)v;
+            const float fv = __builtin_amdgcn_fractf(v);       // v >= 0: v - floor(v)
+            const unsigned o = __umul24((unsigned)iv, pitch16) + boff;
+            const float4* __restrict__ p = reinterpret_cast<const float4*>(smem + o);
+            const float4* __restrict__ n = reinterpret_cast<const float4*>(smem + (o + pitch16));
+            const float4 p00 = p[0], p01 = p[1], p10 = n[0], p11 = n[1];
+            const float w10 = wa * fv, w11 = wb * fv, w00 = wa - w10, w01 = wb - w11;
+            acc[t][q] = fmaf(w11, p11.x, fmaf(w10, p10.x, fmaf(w01, p01.x, fmaf(w00, p00.x, acc[t][q]))));
+            acc[(t + 1) & 3][q] = fmaf(w11, p11.y, fmaf(w10, p10.y, fmaf(w01, p01.y, fmaf(w00, p00.y, acc[(t + 1) & 3][q]))));
+            acc[(t + 2) & 3][q] = fmaf(w11, p11.z, fmaf(w10, p10.z, fmaf(w01, p01.z, fmaf(w00, p00.z, acc[(t + 2) & 3][q]))));
+            acc[(t + 3) & 3][q] = fmaf(w11, p11.w, fmaf(w10, p10.w, fmaf(w01, p01.w, fmaf(w00, p00.w, acc[(t + 3) & 3][q]))));
+        };
+        // clamped into the window whatever the rounding (leaving the clamp out where the first
+        // and last slices' rows lie inside measured no faster)
+#pragma unroll
+        for (int q = 0; q < kConeRotZB; ++q) sample(q, __builtin_amdgcn_fmed3f(fmaf((float)q, a, v0), 0.0f, vmax));
+    };
+    const bool inside = dx < cw && dy < rh;
+    // The items' windows lie at the two ends of the window area in turn, so that one barrier
+    // per item suffices: a wave stores an item's window once every wave is done with the item
+    // before the last (same end).  Two neighbours that do not fit together wait for the reads.
+    int last = 0;
+    auto step = [&](auto turn, int it) {
+        constexpr int t = decltype(turn)::value;
+        const int pitch = nxt.nc, size = nxt.cells;
+        float4* dst = (t & 1) ? win + (job.cap - size) : win;
+        if (last + size > job.cap) __syncthreads();
+        store(dst);
+        __syncthreads();
+        if (it + 1 < items && ((it + 1) & (kConeRotItems - 1))) load(it + 1);
+        if (inside) compute(turn, it, pitch, dst);
+        last = size;
+    };
+    for (int i0 = 0; i0 < items; i0 += kConeRotItems) {
+        __syncthreads();
+        windows(i0);
+        __syncthreads();
+        load(i0);
+        const int end = min(items, i0 + kConeRotItems);
+        for (int it = i0; it < end; it += 4) {
+            step(std::integral_constant<int, 0>{}, it);
+            step(std::integral_constant<int, 1>{}, it + 1);
+            step(std::integral_constant<int, 2>{}, it + 2);
+            step(std::integral_constant<int, 3>{}, it + 3);
+        }
+    }
+
+    // turns 0 and 2 lie along rows; 1 and 3 along columns, transposed through LDS so that
+    // consecutive lanes write consecutive addresses
+    const size_t plane = (size_t)N * N;
+    if (inside) {
+        const int r = r0 + dy, c = c0 + dx;
+#pragma unroll
+        for (int q = 0; q < kConeRotZB; ++q)
+            if (q < zn) {
+                job.vol[(z0 + q) * plane + (size_t)r * N + c] = acc[0][q] * job.scale;
+                job.vol[(z0 + q) * plane + (size_t)(N - 1 - r) * N + (N - 1 - c)] = acc[2][q] * job.scale;
+            }
+    }
+    float* tr = reinterpret_cast<float*>(win);               // [kConeRotZB][16][17]
+#pragma unroll
+    for (int m = 1; m < 4; m += 2) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kConeRotZB; ++q) tr[(q * kConeTile + dx) * (kConeTile + 1) + dy] = acc[m][q];
+        __syncthreads();
+        // lane (dx, dy) now holds column c0 + dy, row r0 + dx of the tile
+        if (dy < cw && dx < rh) {
+            const int r = r0 + dx, c = c0 + dy;
+            const size_t o = m == 1 ? (size_t)c * N + (N - 1 - r) : (size_t)(N - 1 - c) * N + r;
+#pragma unroll
+            for (int q = 0; q < kConeRotZB; ++q)
+                if (q < zn) job.vol[(z0 + q) * plane + o] = tr[(q * kConeTile + dy) * (kConeTile + 1) + dx] * job.scale;
+        }
+    }
+}
+
+// Odd N: the centre column (x = y = 0, so rho = 1 and u = (Du-1)/2 on every view), one
+// slice per lane, all views in order.
+__global__ __launch_bounds__(kConeThreads) void cone_centre_kernel(ConeJob job) {
+    const int z = blockIdx.x * kConeThreads + threadIdx.x;
+    if (z >= job.Nz) return;                                 // no barrier follows
+    const double v = ((double)z - job.half_z) / job.dv + job.cv, u = job.cu;
+    const int j0 = (int)floor(v), i0 = (int)floor(u);
+    const float fv = (float)(v - (double)j0), fu = (float)(u - (double)i0);
+    auto at = [&](const float* q, int row, int col) {
+        return (unsigned)row < (unsigned)job.Dv && (unsigned)col < (unsigned)job.Du ? q[(size_t)row * job.Du + col] : 0.0f;
+    };
+    float sum = 0.0f;
+#pragma unroll 8
+    for (int k = 0; k < job.K; ++k) {
+        const float* q = job.q + (size_t)k * job.Dv * job.Du;
+        const float a = fmaf(fu, at(q, j0, i0 + 1), (1.0f - fu) * at(q, j0, i0));
+        const float b = fmaf(fu, at(q, j0 + 1, i0 + 1), (1.0f - fu) * at(q, j0 + 1, i0));
+        sum += fmaf(fv, b, (1.0f - fv) * a);
+    }
+    const int c = job.N >> 1;
+    job.vol[((size_t)z * job.N + c) * job.N + c] = sum * job.scale;
+}
+
 // fixed row pitches (floats) of the staged windows; the second row of a bilinear
 // sample sits at an LDS offset of P + 1 <= 255 dwords
 constexpr int kConePitches[] = {16, 24, 32, 40, 48, 64, 80, 96, 128, 160, 192, 248};
@@ -301,6 +580,31 @@ int cone_pitch(int WL) {
 size_t cone_lds_bytes(int KB, int cap, bool staged) {
     return sizeof(float) * kConeCoef * (size_t)KB + sizeof(int) * 8 * (size_t)KB + sizeof(int) * 4 +
            (staged ? sizeof(float) * (size_t)cap : 0);
+}
+
+// LDS of a workgroup whose window area holds `cells` cells (and, at the end, the
+// transposed voxels of one turn)
+size_t cone_rot_lds_bytes(int cells) {
+    const int least = kConeRotZB * kConeTile * (kConeTile + 1) / 4;
+    return sizeof(float) * kConeRotInts * kConeRotItems + sizeof(float4) * (size_t)std::max(cells, least);
+}
+
+hipError_t launch_cone_rot(ConeJob job, hipStream_t stream) {
+    if (job.N < 2 || job.K % 4 != 0 || job.WL < 2 || job.WV < 2 ||
+        cone_rot_lds_bytes((job.WL + 1) * (job.WV + 1)) > kConeLdsBudget)
+        return hipErrorInvalidValue;
+    // room for two of the largest windows, up to a quarter of a CU's LDS
+    job.cap = std::min(2 * (job.WL + 1) * (job.WV + 1), (int)((kConeLdsBudget - sizeof(float) * kConeRotInts * kConeRotItems) / sizeof(float4)));
+    job.cap = std::max(job.cap, (job.WL + 1) * (job.WV + 1));
+    const size_t lds = cone_rot_lds_bytes(job.cap);
+    if ((int64_t)job.Dv * job.Du * 4 > 0x7FFFFFF0) return hipErrorInvalidValue;     // a view's buffer range
+    const int64_t tiles = (int64_t)job.tiles_x * (((job.N >> 1) + kConeTile - 1) / kConeTile);
+    const int64_t blocks = tiles * ((job.Nz + kConeRotZB - 1) / kConeRotZB);
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const hipError_t e = launch_kernel(cone_rot_kernel, dim3((unsigned)blocks), dim3(kConeThreads), lds, stream, job);
+    if (e != hipSuccess || !(job.N & 1)) return e;
+    return launch_kernel(cone_centre_kernel, dim3((unsigned)((job.Nz + kConeThreads - 1) / kConeThreads)), dim3(kConeThreads),
+                         0, stream, job);
 }
 
 hipError_t launch_cone_bp(const ConeJob& job, bool staged, hipStream_t stream) {

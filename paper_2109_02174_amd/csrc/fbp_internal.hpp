@@ -356,6 +356,11 @@ size_t cone_lds_bytes(int KB, int cap, bool staged);
 // staged: detector windows through LDS (cap floats, which must hold the largest
 // window of WV + 1 rows of pitch floats); otherwise values are read from global memory.
 hipError_t launch_cone_bp(const ConeJob& job, bool staged, hipStream_t stream);
+// Quarter-turn form (N >= 2; K = 4 K4 with view k + j K4 at angle b_k + j pi/2): WL and WV
+// bound the windows of kConeRotZB slices, tiles_x = ceil(((N+1)/2) / kConeTile).
+constexpr int kConeRotZB = 16;       // slices per workgroup
+size_t cone_rot_lds_bytes(int cells);
+hipError_t launch_cone_rot(ConeJob job, hipStream_t stream);
 
 // ------------------------------------------------------------------ ramp filter GEMM
 

@@ -1853,6 +1853,8 @@ struct ConePlan {
     float* d_pw = nullptr;
     int WL = 0, WV = 0, KB = 0, pitch = 0, cap = 0;
     bool staged = true;
+    bool rot = false;                // quarter-turn form
+    int rot_WV = 0;                  // its row bound
     double half_span = 0.0;
     RowScratch rows;
 };
@@ -1890,6 +1892,13 @@ int make_cone_plan(ConePlan* c) {
     c->KB = 16;
     c->cap = (int)((kConeLdsBudget - cone_lds_bytes(c->KB, 0, false)) / sizeof(float));
     c->staged = (int64_t)(c->WV + 1) * c->pitch <= c->cap;   // windows through LDS, else direct reads
+    // quarter-turn lists: the windows of kConeRotZB slices as cells of four views, where
+    // the largest fits the workgroup's LDS
+    const double rot_v = ((double)(kConeRotZB - 1) * rho_max + 0.5 * (double)(c->Nz - 1) * drho) / c->dv;
+    c->rot_WV = (int)std::ceil(rot_v) + 5;
+    c->rot = c->N >= 2 && fan_quarter_turns(c->angles) && (int64_t)(c->WL + 1) * (c->rot_WV + 1) < 65536 &&
+             cone_rot_lds_bytes((c->WL + 1) * (c->rot_WV + 1)) <= kConeLdsBudget &&
+             (int64_t)c->Dv * c->Du * 4 <= 0x7FFFFFF0;
     std::vector<double> cs(2 * (size_t)c->K);
     for (int k = 0; k < c->K; ++k) {
         cs[2 * k] = std::cos(c->angles[k]);
@@ -2034,7 +2043,11 @@ int run_cone_backproject(const ConePlan& c, const float* filt, float* vol, hipSt
              reinterpret_cast<uintptr_t>(filt) % 16 == 0;
     j.tiles_x = (c.N + kConeTile - 1) / kConeTile;
     j.scale = (float)(2.0 * kPi / (double)c.K);
-    const hipError_t e = launch_cone_bp(j, c.staged, s);
+    if (c.rot) {
+        j.WV = c.rot_WV;
+        j.tiles_x = ((c.N + 1) / 2 + kConeTile - 1) / kConeTile;
+    }
+    const hipError_t e = c.rot ? launch_cone_rot(j, s) : launch_cone_bp(j, c.staged, s);
     return e == hipErrorInvalidValue ? FBP_EUNSUPPORTED : hip_status(e, "cone-beam backprojection launch");
 }
 

@@ -1,0 +1,58 @@
+"""GPU: the quarter-turn cone-beam backprojector at the edges of its tiles.
+
+View lists closed under quarter turns go through workgroups that own a 16 x 16 tile of the
+base region, its three turns and 16 slices, with windows of four views in LDS.  The cases:
+sides on both sides of the base tile (odd ones with the centre column), depths on both
+sides of the slice block, unsorted quarters, windows past the detector's edges, windows
+larger than the prefetch and than half of the LDS, and a list that is not closed (the
+general kernel).  Reference and tolerance: those of the cone backprojection's parity test.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2109_02174_amd as fbp
+from paper_2109_02174_amd import phantom as ph
+
+pytestmark = pytest.mark.gpu
+
+
+def _tol(Q, N, Nz, dv, R):
+    Q = np.asarray(Q, np.float64)
+    M = R / (R - (N - 1) / math.sqrt(2.0))
+    dq = max(np.max(np.abs(np.diff(Q, axis=-1))) if Q.shape[-1] > 1 else 0.0,
+             np.max(np.abs(np.diff(Q, axis=-2))) if Q.shape[-2] > 1 else 0.0)
+    zmax = 0.5 * (Nz - 1)
+    return 2.0 * math.pi * M * M * (1e-5 * (1.0 + zmax * M / dv / 16.0) * max(dq, np.max(np.abs(Q))) +
+                                    1e-6 * np.max(np.abs(Q))) + 1e-6
+
+
+@pytest.mark.parametrize("K,Dv,Du,N,Nz,du,dv,Rf,kind", [
+    (4, 9, 9, 2, 3, 1.0, 1.0, 3.0, "turn"),            # one pixel per turn, one base view
+    (8, 9, 9, 3, 1, 1.0, 1.0, 3.0, "quarter"),         # a centre column, one slice
+    (12, 40, 50, 32, 16, 1.0, 1.0, 2.0, "turn"),       # one base tile, one block of slices
+    (12, 41, 51, 33, 17, 1.0, 1.0, 2.0, "quarter"),    # one more of each
+    (16, 40, 50, 31, 15, 1.0, 1.0, 2.0, "quarter"),    # one fewer
+    (36, 50, 70, 49, 40, 1.0, 1.0, 1.6, "turn"),       # nine items' worth of views past a block of windows
+    (8, 20, 26, 34, 33, 1.0, 1.0, 2.0, "turn"),        # windows past every detector edge
+    (8, 90, 130, 40, 48, 0.5, 0.6, 1.9, "quarter"),    # fine detector: large windows
+    (8, 120, 90, 36, 100, 1.0, 0.8, 1.3, "turn"),      # tall volume, source close
+    (10, 41, 51, 33, 17, 1.0, 1.0, 2.0, "turn"),       # not closed: the general kernel
+])
+def test_quarter_turn_cone_backprojection_matches_oracle(K, Dv, Du, N, Nz, du, dv, Rf, kind):
+    R = Rf * N * math.sqrt(0.5) + 1.0
+    if kind == "turn":
+        b = np.arange(K) * (2.0 * math.pi / K)
+    else:
+        q = ph.rng_for(1810, K * N).uniform(-math.pi, math.pi, K // 4)
+        b = np.concatenate([q + j * 0.5 * math.pi for j in range(4)])
+    g = fbp.ConeGeometry(K, Du, Dv, N, Nz, R, du, dv, angles=b)
+    Q = ph.rng_for(1811, K + N).normal(size=(K, Dv, Du)).astype(np.float32)
+    out = torch.full(g.volume_shape(), float("nan"), device="cuda")
+    fbp.fbp_cone_backproject(g, torch.tensor(Q, device="cuda"), out=out)
+    ref = oracle.cone_backproject(Q.astype(np.float64), N, Nz, du, dv, R, b)
+    got = out.cpu().numpy()
+    assert np.max(np.abs(got - ref)) <= _tol(Q, N, Nz, dv, R)
