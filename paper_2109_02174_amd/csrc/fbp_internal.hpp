@@ -182,6 +182,7 @@ struct ProjJob {
     int32_t N, K, D;
     float scale;          // pi/K
     int32_t T;            // pixels read per line
+    int32_t fast3;        // 1: three taps, 1 <= r <= 1.5 on every angle
     int32_t pad, pitch;   // zeros before each line; floats per padded line
 };
 // One base angle phi of the staged projector: a turn of the list's angle theta_{k0} by

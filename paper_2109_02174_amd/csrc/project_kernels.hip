@@ -12,8 +12,8 @@
 // pixels with a nonzero weight are the integers in (p* - r, p* + r), r = 1/|a| with a
 // the slope of u along the line: at most T = ceil(2r), T consecutive pixels from
 // floor(p* - r) + 1.  Each bin is written once; no atomics; fixed summation order.
-// Two forms: the staged projector (image rows through LDS, several bins per walk) for
-// up to four taps whose windows fit its LDS rows, and project_kernel for the rest.
+// Two forms: the staged projector (image rows through LDS, several bins per walk) where
+// neighbouring angles share a window of its LDS rows, and project_kernel for the rest.
 #include "fbp_internal.hpp"
 
 #include <algorithm>
@@ -683,17 +683,22 @@ __global__ __launch_bounds__(256) void transpose_kernel(const float* __restrict_
         if (c0 + ty + i < N && r0 + tx < N) dst[(size_t)(c0 + ty + i) * N + r0 + tx] = tile[tx][ty + i];
 }
 
-// ---------------------------------------------------------------- any detector spacing
+// ---------------------------------------------------------------- one lane per bin
 //
-// Taps counted at run time: the detectors whose windows are too wide to stage (five or
-// more pixels per line).  Rows when |cos| >= |sin|, else columns.  The slice is first
-// copied twice, rows and transposed, each line padded with zeros on both sides (pad P)
-// and followed by one zero line, so that both walks read along memory and a lane's
-// window never needs a bounds test.  p* advances by the same step on every line, so it
-// is carried in 32.32 fixed point (integer part = window start, fraction = phase of the
-// window), re-anchored from FP64 every 256 lines.  A wave walks only the lines its 64
-// bins can reach; on those every bin of the wave lies within 65 r + 3 pixels of the
+// Lists too sparse for neighbouring angles to share a staged window, small images (where
+// both take the time of their launches), and detectors too coarse to stage (five or more
+// taps).  Rows when |cos| >= |sin|, else columns.  The slice is first copied twice, rows
+// and transposed, each line padded with zeros on both sides (pad P) and followed by one
+// zero line, so that both walks read along memory and a lane's window never needs a bounds
+// test.  p* advances by the same step on every line, so it is carried in 32.32 fixed point
+// (integer part = window start, fraction = phase of the window), stepped with a 64-bit
+// integer add and re-anchored from FP64 every 256 lines.  A wave walks only the lines its
+// 64 bins can reach; on those every bin of the wave lies within 65 r + 3 pixels of the
 // image (it is within 63 bins of one that reaches it), which bounds the pad.
+// Taps of one line: T > 0 fixed, T == 0 job.T at run time.  FAST3: three taps
+// with 1 <= r <= 1.5 on every angle (unit detector spacing), where the first tap
+// lies left of p* and the third right of it, so only the middle one needs |.|.
+template <int T, bool FAST3>
 __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjJob job) {
     // block b: (slice, angle, block of 256 bins), bins fastest
     const int nbj = (job.D + kProjThreads - 1) / kProjThreads;
@@ -704,7 +709,7 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjJob job) {
     if (jw >= job.D) return;                        // whole wave past the last bin
     const int j = jw + (threadIdx.x & 63);
     const int N = job.N;
-    const int taps = job.T;
+    const int taps = T > 0 ? T : job.T;
     const double c = job.cs[2 * k];                 // cos/dt
     const double sn = job.cs[2 * k + 1];            // sin/dt
     const double half = job.half_pix;               // (N-1)/2
@@ -753,17 +758,81 @@ __global__ __launch_bounds__(kProjThreads) void project_kernel(ProjJob job) {
         };
         const uint64_t step = (uint64_t)(int64_t)llrint(dl * kTwo32);
         const uint32_t st_max = (uint32_t)(pitch - taps);
+        const float aa = (float)fabs(a);
+        const float na = (float)(-fabs(a) / kTwo32), pa = (float)(fabs(a) / kTwo32);
+        const float c1 = (float)(fabs(a) * (2.0 - r)), c2 = (float)(2.0 - 3.0 * fabs(a));
         const float sa = (float)(-a / kTwo32);
-        uint64_t x = anchor(l_lo);
-        for (int l = l_lo; l <= l_hi; ++l, line += pitch) {
-            if (l != l_lo) x = ((l & (kAnchorLines - 1)) == 0) ? anchor(l) : x + step;
-            const uint32_t st = min((uint32_t)(x >> 32), st_max);    // in bounds whatever x holds
-            const float ph = (float)(uint32_t)x;                     // phase * 2^32
-            const float* __restrict__ px = line + st;
-            for (int m = 0; m < taps; ++m) {
-                const float t = fmaf(sa, ph, (float)(a * (1.0 - r + (double)m)));   // a (tap - p*)
-                const float w = __builtin_amdgcn_fmed3f(1.0f - fabsf(t), 0.0f, 1.0f);
-                acc = fmaf(w, px[m], acc);
+        float cm[T > 0 ? T : 1];                    // a (1 - r + m): hat argument of tap m at phase 0
+        if constexpr (T > 0) {
+#pragma unroll
+            for (int m = 0; m < T; ++m) cm[m] = (float)(a * (1.0 - r + (double)m));
+        }
+        if constexpr (T > 0) {
+            auto load = [&](const float* ln, uint64_t x, float& ph, float (&v)[T]) {
+                const uint32_t st = min((uint32_t)(x >> 32), st_max);    // in bounds whatever x holds
+                ph = (float)(uint32_t)x;                                  // phase * 2^32
+                const float* __restrict__ px = ln + st;
+#pragma unroll
+                for (int m = 0; m < T; ++m) v[m] = px[m];        // one T-dword load
+            };
+            auto accumulate = [&](float ph, const float (&v)[T]) {
+                if constexpr (FAST3) {
+                    const float w0 = fmaf(na, ph, aa);                    // |a| (1 - phase)
+                    const float w1 = 1.0f - fabsf(fmaf(na, ph, c1));
+                    const float w2 = __builtin_amdgcn_fmed3f(fmaf(pa, ph, c2), 0.0f, 1.0f);
+                    acc = fmaf(w0, v[0], acc);
+                    acc = fmaf(w1, v[1], acc);
+                    acc = fmaf(w2, v[2], acc);
+                } else {
+#pragma unroll
+                    for (int m = 0; m < T; ++m) {
+                        const float t = fmaf(sa, ph, cm[m]);              // a (tap - p*)
+                        const float w = __builtin_amdgcn_fmed3f(1.0f - fabsf(t), 0.0f, 1.0f);
+                        acc = fmaf(w, v[m], acc);
+                    }
+                }
+            };
+            // lines in runs of kAnchorLines from an FP64 anchor; four lines per round,
+            // all four loads issued before the first line's weights
+            for (int l0 = l_lo; l0 <= l_hi; l0 += kAnchorLines) {
+                const int l1 = min(l0 + kAnchorLines - 1, l_hi);
+                uint64_t x = anchor(l0);
+                int l = l0;
+                for (; l + 3 <= l1; l += 4) {
+                    float ph[4];
+                    float v[4][T];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        load(line + u * pitch, x, ph[u], v[u]);
+                        x += step;
+                        asm volatile("" : "+v"(x));         // one 64-bit add per line, no unrolled copies
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) accumulate(ph[u], v[u]);
+                    line += 4 * pitch;
+                }
+                for (; l <= l1; ++l) {
+                    float ph;
+                    float v[T];
+                    load(line, x, ph, v);
+                    accumulate(ph, v);
+                    x += step;
+                    asm volatile("" : "+v"(x));
+                    line += pitch;
+                }
+            }
+        } else {
+            uint64_t x = anchor(l_lo);
+            for (int l = l_lo; l <= l_hi; ++l, line += pitch) {
+                if (l != l_lo) x = ((l & (kAnchorLines - 1)) == 0) ? anchor(l) : x + step;
+                const uint32_t st = min((uint32_t)(x >> 32), st_max);
+                const float ph = (float)(uint32_t)x;
+                const float* __restrict__ px = line + st;
+                for (int m = 0; m < taps; ++m) {
+                    const float t = fmaf(sa, ph, (float)(a * (1.0 - r + (double)m)));
+                    const float w = __builtin_amdgcn_fmed3f(1.0f - fabsf(t), 0.0f, 1.0f);
+                    acc = fmaf(w, px[m], acc);
+                }
             }
         }
     }
@@ -1095,7 +1164,18 @@ hipError_t launch_project(const ProjJob& job, int n_slices, hipStream_t stream) 
     if (job.T < 1 || job.pitch < job.N + 2 * job.T || job.pad < job.T) return hipErrorInvalidValue;
     const int64_t blocks = (int64_t)((job.D + kProjThreads - 1) / kProjThreads) * job.K * n_slices;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    return launch_kernel(project_kernel, dim3((unsigned)blocks), dim3(kProjThreads), 0, stream, job);
+    const dim3 grid((unsigned)blocks), block(kProjThreads);
+    if (job.fast3) {
+        if (job.T != 3) return hipErrorInvalidValue;
+        return launch_kernel(project_kernel<3, true>, grid, block, 0, stream, job);
+    }
+    switch (job.T) {
+        case 1: return launch_kernel(project_kernel<1, false>, grid, block, 0, stream, job);
+        case 2: return launch_kernel(project_kernel<2, false>, grid, block, 0, stream, job);
+        case 3: return launch_kernel(project_kernel<3, false>, grid, block, 0, stream, job);
+        case 4: return launch_kernel(project_kernel<4, false>, grid, block, 0, stream, job);
+        default: return launch_kernel(project_kernel<0, false>, grid, block, 0, stream, job);
+    }
 }
 
 hipError_t launch_fan_project(const FanProjJob& job, int n_slices, hipStream_t stream) {

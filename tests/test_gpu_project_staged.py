@@ -55,6 +55,15 @@ def _angles(K, kind, seed):
     (37, 60, 70, 1.9, 1, "random"),      # too coarse to stage
     (36, 24, 90, 6.0, 1, "uniform"),
     (720, 181, 128, 1.0, 1, "uniform"),
+    (720, 159, 112, 1.0, 1, "uniform"),  # the smallest staged image; half detector of 80 bins
+    (720, 161, 113, 1.0, 2, "uniform"),  # one bin and one row more
+    (720, 160, 111, 1.0, 1, "uniform"),  # one below the smallest
+    (300, 183, 128, 1.0, 3, "uniform"),  # four angles share a window
+    (1001, 190, 130, 1.0, 2, "golden"),  # eight, two bins per angle
+    (1001, 190, 130, 1.0, 1, "uniform"),
+    (720, 300, 112, 0.6, 1, "uniform"),  # two taps
+    (720, 400, 113, 0.45, 1, "uniform"),   # one tap
+    (720, 140, 127, 1.3, 1, "uniform"),  # four taps
 ])
 def test_staged_projector_matches_oracle(K, D, N, dt, B, kind):
     ang = _angles(K, kind, K * D + N)
