@@ -105,8 +105,10 @@ __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
     int* nk_lds = org + 8 * KB;
     float* win = reinterpret_cast<float*>(nk_lds + 4);
     const int tiles = job.tiles_x * job.tiles_x;
-    const int zb = blockIdx.x / tiles;
-    const int tile = blockIdx.x - zb * tiles;
+    const int zblocks = (job.Nz + kConeZB - 1) / kConeZB;
+    const int view_part = blockIdx.x / (tiles * zblocks);              // views [K part / split, K (part+1) / split)
+    const int zb = blockIdx.x / tiles - view_part * zblocks;
+    const int tile = blockIdx.x % tiles;
     const int c0 = (tile % job.tiles_x) * kConeTile, r0 = (tile / job.tiles_x) * kConeTile;
     const int z0 = zb * kConeZB;
     const int zn = min(kConeZB, job.Nz - z0);
@@ -119,8 +121,9 @@ __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
     float acc[kConeZB];
 #pragma unroll
     for (int q = 0; q < kConeZB; ++q) acc[q] = 0.0f;
-    for (int k0 = 0; k0 < K;) {
-        const int nmax = min(KB, K - k0);
+    const int k_end = (int)((int64_t)K * (view_part + 1) / job.split);
+    for (int k0 = (int)((int64_t)K * view_part / job.split); k0 < k_end;) {
+        const int nmax = min(KB, k_end - k0);
         __syncthreads();                                // previous block's reads done
         if (threadIdx.x < 64) {                         // wave 0: one view per lane (KB <= 64)
             int size = 0;
@@ -268,10 +271,13 @@ __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
         k0 += nk;
     }
     if (inside) {
+        // split views: unscaled sums into the part's plane
+        float* __restrict__ vol = job.split > 1 ? job.part + (size_t)view_part * job.Nz * N * N : job.vol;
+        const float scale = job.split > 1 ? 1.0f : job.scale;
 #pragma unroll
         for (int q = 0; q < kConeZB; ++q)
             if (q < zn)
-                job.vol[((size_t)(z0 + q) * N + (r0 + dy)) * N + (c0 + dx)] = acc[q] * job.scale;
+                vol[((size_t)(z0 + q) * N + (r0 + dy)) * N + (c0 + dx)] = acc[q] * scale;
     }
 }
 
@@ -306,8 +312,10 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
     float4* win = reinterpret_cast<float4*>(coef + kConeRotInts * kConeRotItems);
     const int tiles_y = ((N >> 1) + kConeTile - 1) / kConeTile;
     const int tiles = job.tiles_x * tiles_y;
-    const int zb = blockIdx.x / tiles;
-    const int tile = blockIdx.x - zb * tiles;
+    const int zblocks = (job.Nz + kConeRotZB - 1) / kConeRotZB;
+    const int view_part = blockIdx.x / (tiles * zblocks);    // base views [K4 part / split, K4 (part+1) / split)
+    const int zb = blockIdx.x / tiles - view_part * zblocks;
+    const int tile = blockIdx.x % tiles;
     const int c0 = (tile % job.tiles_x) * kConeTile, r0 = (tile / job.tiles_x) * kConeTile;
     const int z0 = zb * kConeRotZB;
     const int zn = min(kConeRotZB, job.Nz - z0);
@@ -318,7 +326,8 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
     const float fdx = (float)dx, fdy = (float)dy;
     const double zlo = (double)z0 - job.half_z, zhi = zlo + (double)(zn - 1);
     const float zlo_dv = (float)(zlo / job.dv), inv_dv = (float)(1.0 / job.dv);
-    const int items = 4 * K4;
+    const int first = 4 * (int)((int64_t)K4 * view_part / job.split);
+    const int items = 4 * (int)((int64_t)K4 * (view_part + 1) / job.split);      // one past the last
     const size_t view = (size_t)Dv * Du;
 
     float acc[4][kConeRotZB];
@@ -385,7 +394,7 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
         float inv_nc;
     };
     auto window = [&](int it) {
-        const int* og = reinterpret_cast<const int*>(coef + kConeRotInts * (it & (kConeRotItems - 1)) + 9);
+        const int* og = reinterpret_cast<const int*>(coef + kConeRotInts * ((it - first) & (kConeRotItems - 1)) + 9);
         Window w;
         w.i0 = __builtin_amdgcn_readfirstlane(og[0]);
         w.j0 = __builtin_amdgcn_readfirstlane(og[1]);
@@ -434,7 +443,7 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
     };
     auto compute = [&](auto turn, int it, int pitch, const float4* cells) {
         constexpr int t = decltype(turn)::value;
-        const float* cf = coef + kConeRotInts * (it & (kConeRotItems - 1));
+        const float* cf = coef + kConeRotInts * ((it - first) & (kConeRotItems - 1));
         const float4 nf = *reinterpret_cast<const float4*>(cf);
         const float4 df = *reinterpret_cast<const float4*>(cf + 4);
         const float vmax = cf[8];
@@ -483,11 +492,11 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
         if (last + size > job.cap) __syncthreads();
         store(dst);
         __syncthreads();
-        if (it + 1 < items && ((it + 1) & (kConeRotItems - 1))) load(it + 1);
+        if (it + 1 < items && ((it + 1 - first) & (kConeRotItems - 1))) load(it + 1);
         if (inside) compute(turn, it, pitch, dst);
         last = size;
     };
-    for (int i0 = 0; i0 < items; i0 += kConeRotItems) {
+    for (int i0 = first; i0 < items; i0 += kConeRotItems) {
         __syncthreads();
         windows(i0);
         __syncthreads();
@@ -504,13 +513,15 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
     // turns 0 and 2 lie along rows; 1 and 3 along columns, transposed through LDS so that
     // consecutive lanes write consecutive addresses
     const size_t plane = (size_t)N * N;
+    float* __restrict__ vol = job.split > 1 ? job.part + (size_t)view_part * job.Nz * plane : job.vol;
+    const float scale = job.split > 1 ? 1.0f : job.scale;      // split views: unscaled sums into the part's plane
     if (inside) {
         const int r = r0 + dy, c = c0 + dx;
 #pragma unroll
         for (int q = 0; q < kConeRotZB; ++q)
             if (q < zn) {
-                job.vol[(z0 + q) * plane + (size_t)r * N + c] = acc[0][q] * job.scale;
-                job.vol[(z0 + q) * plane + (size_t)(N - 1 - r) * N + (N - 1 - c)] = acc[2][q] * job.scale;
+                vol[(z0 + q) * plane + (size_t)r * N + c] = acc[0][q] * scale;
+                vol[(z0 + q) * plane + (size_t)(N - 1 - r) * N + (N - 1 - c)] = acc[2][q] * scale;
             }
     }
     float* tr = reinterpret_cast<float*>(win);               // [kConeRotZB][16][17]
@@ -526,7 +537,7 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
             const size_t o = m == 1 ? (size_t)c * N + (N - 1 - r) : (size_t)(N - 1 - c) * N + r;
 #pragma unroll
             for (int q = 0; q < kConeRotZB; ++q)
-                if (q < zn) job.vol[(z0 + q) * plane + o] = tr[(q * kConeTile + dy) * (kConeTile + 1) + dx] * job.scale;
+                if (q < zn) vol[(z0 + q) * plane + o] = tr[(q * kConeTile + dy) * (kConeTile + 1) + dx] * scale;
         }
     }
 }
@@ -599,10 +610,13 @@ hipError_t launch_cone_rot(ConeJob job, hipStream_t stream) {
     const size_t lds = cone_rot_lds_bytes(job.cap);
     if ((int64_t)job.Dv * job.Du * 4 > 0x7FFFFFF0) return hipErrorInvalidValue;     // a view's buffer range
     const int64_t tiles = (int64_t)job.tiles_x * (((job.N >> 1) + kConeTile - 1) / kConeTile);
-    const int64_t blocks = tiles * ((job.Nz + kConeRotZB - 1) / kConeRotZB);
+    if (job.split < 1 || job.split > job.K / 4 || (job.split > 1 && !job.part)) return hipErrorInvalidValue;
+    const int64_t blocks = tiles * ((job.Nz + kConeRotZB - 1) / kConeRotZB) * job.split;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    const hipError_t e = launch_kernel(cone_rot_kernel, dim3((unsigned)blocks), dim3(kConeThreads), lds, stream, job);
-    if (e != hipSuccess || !(job.N & 1)) return e;
+    return launch_kernel(cone_rot_kernel, dim3((unsigned)blocks), dim3(kConeThreads), lds, stream, job);
+}
+
+hipError_t launch_cone_centre(const ConeJob& job, hipStream_t stream) {
     return launch_kernel(cone_centre_kernel, dim3((unsigned)((job.Nz + kConeThreads - 1) / kConeThreads)), dim3(kConeThreads),
                          0, stream, job);
 }
@@ -616,7 +630,8 @@ hipError_t launch_cone_bp(const ConeJob& job, bool staged, hipStream_t stream) {
     if (staged && (int64_t)(job.WV + 1) * job.pitch > job.cap) return hipErrorInvalidValue;   // one window must fit
     const size_t lds = cone_lds_bytes(job.KB, job.cap, staged);
     if (lds > kConeLdsBudget) return hipErrorInvalidValue;
-    const int64_t blocks = (int64_t)job.tiles_x * job.tiles_x * ((job.Nz + kConeZB - 1) / kConeZB);
+    if (job.split < 1 || job.split > job.K || (job.split > 1 && !job.part)) return hipErrorInvalidValue;
+    const int64_t blocks = (int64_t)job.tiles_x * job.tiles_x * ((job.Nz + kConeZB - 1) / kConeZB) * job.split;
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     return staged ? launch_pitch<0>(job.pitch, job, grid, lds, stream)

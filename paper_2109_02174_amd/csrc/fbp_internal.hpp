@@ -345,6 +345,8 @@ struct ConeJob {
     int32_t vec4;          // stage groups of four columns (Du, pitch multiples of 4, q 16-byte aligned,
                            // pitch >= WL + 7 for the wider aligned windows)
     int32_t tiles_x;       // ceil(N / kConeTile)
+    int32_t split;         // parts the views are split over (1: none)
+    float* part;           // split > 1: [split][Nz][N][N] unscaled partial sums
     float scale;           // 2 pi / K
 };
 constexpr int kConeTile = 16;
@@ -362,6 +364,8 @@ hipError_t launch_cone_bp(const ConeJob& job, bool staged, hipStream_t stream);
 constexpr int kConeRotZB = 16;       // slices per workgroup
 size_t cone_rot_lds_bytes(int cells);
 hipError_t launch_cone_rot(ConeJob job, hipStream_t stream);
+// The centre column of odd N, which launch_cone_rot leaves out (written last).
+hipError_t launch_cone_centre(const ConeJob& job, hipStream_t stream);
 
 // ------------------------------------------------------------------ ramp filter GEMM
 

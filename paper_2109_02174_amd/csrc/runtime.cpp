@@ -1836,6 +1836,8 @@ size_t cone_vol_bytes(const fbp_cone_geom* g) {
     return sizeof(float) * (size_t)g->volume_depth * (size_t)g->volume_size * (size_t)g->volume_size;
 }
 
+constexpr size_t kConePartBytes = (size_t)64 << 20;   // most bytes of a plan's partial volumes
+
 struct ConeKey {
     int device, K, Du, Dv, N, Nz, filter;
     uint64_t du_bits, dv_bits, r_bits, angle_hash;
@@ -1850,6 +1852,7 @@ struct ConeKey {
 // R / sqrt(R^2 + s^2 + z^2) per detector cell, the staged window bounds and a
 // scratch buffer for the pre-weighted views.
 struct ConePlan {
+    int device = 0;
     int K = 0, Du = 0, Dv = 0, N = 0, Nz = 0, filter = 0;
     double du = 1.0, dv = 1.0, R = 0.0;
     std::vector<double> angles;
@@ -1860,6 +1863,7 @@ struct ConePlan {
     bool staged = true;
     bool rot = false;                // quarter-turn form
     int rot_WV = 0;                  // its row bound
+    PartBuffer part;                 // small volumes: partial sums of the view parts (planes = parts)
     double half_span = 0.0;
     RowScratch rows;
 };
@@ -1904,6 +1908,18 @@ int make_cone_plan(ConePlan* c) {
     c->rot = c->N >= 2 && fan_quarter_turns(c->angles) && (int64_t)(c->WL + 1) * (c->rot_WV + 1) < 65536 &&
              cone_rot_lds_bytes((c->WL + 1) * (c->rot_WV + 1)) <= kConeLdsBudget &&
              (int64_t)c->Dv * c->Du * 4 <= 0x7FFFFFF0;
+    // Small volumes leave CUs idle and each workgroup a long serial walk over the views (32^3,
+    // 310 views: 4 workgroups, 585 us): the views are split over up to kMaxSplit parts for
+    // about four workgroups per CU, summed in part order (at most kConePartBytes of sums)
+    const int ty = c->rot ? (c->N / 2 + kConeTile - 1) / kConeTile : (c->N + kConeTile - 1) / kConeTile;
+    const int tx = c->rot ? ((c->N + 1) / 2 + kConeTile - 1) / kConeTile : ty;
+    const int zb = c->rot ? kConeRotZB : kConeZB;
+    const int64_t blocks = (int64_t)tx * ty * ((c->Nz + zb - 1) / zb), cus = cu_count(c->device);
+    const size_t vol = sizeof(float) * (size_t)c->Nz * (size_t)c->N * (size_t)c->N;
+    if (blocks <= 2 * cus) {
+        const int64_t most = std::min<int64_t>({kMaxSplit, c->K / 8, (int64_t)(kConePartBytes / vol)});
+        c->part.planes = (int)std::max<int64_t>(1, std::min<int64_t>(most, (4 * cus + blocks - 1) / blocks));
+    }
     std::vector<double> cs(2 * (size_t)c->K);
     for (int k = 0; k < c->K; ++k) {
         cs[2 * k] = std::cos(c->angles[k]);
@@ -1922,7 +1938,13 @@ int make_cone_plan(ConePlan* c) {
     if (e == hipSuccess) e = hipMemcpy(c->d_cs, cs.data(), sizeof(double) * cs.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_pw, pw.data(), sizeof(float) * pw.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->rows.free_ev, hipEventDisableTiming);
+    if (e == hipSuccess && c->part.planes > 1) {
+        e = hipMalloc(&c->part.ptr, vol * (size_t)c->part.planes);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&c->part.free_ev, hipEventDisableTiming);
+    }
     if (e != hipSuccess) {
+        if (c->part.ptr) (void)hipFree(c->part.ptr);
+        c->part.ptr = nullptr;
         if (c->d_cs) (void)hipFree(c->d_cs);
         if (c->d_pw) (void)hipFree(c->d_pw);
         c->d_cs = nullptr;
@@ -1964,6 +1986,7 @@ int get_cone_plan(const fbp_cone_geom* g, ConePlan** out) {
         return FBP_OK;
     }
     auto c = std::make_unique<ConePlan>();
+    c->device = device;
     c->K = g->n_views;
     c->Du = g->n_det_u;
     c->Dv = g->n_det_v;
@@ -2019,7 +2042,7 @@ int run_cone_filter(ConePlan& c, const float* proj, float* filt, hipStream_t s) 
     return FBP_OK;
 }
 
-int run_cone_backproject(const ConePlan& c, const float* filt, float* vol, hipStream_t s) {
+int run_cone_backproject(ConePlan& c, const float* filt, float* vol, hipStream_t s) {
     ConeJob j{};
     j.q = filt;
     j.vol = vol;
@@ -2052,7 +2075,29 @@ int run_cone_backproject(const ConePlan& c, const float* filt, float* vol, hipSt
         j.WV = c.rot_WV;
         j.tiles_x = ((c.N + 1) / 2 + kConeTile - 1) / kConeTile;
     }
-    const hipError_t e = c.rot ? launch_cone_rot(j, s) : launch_cone_bp(j, c.staged, s);
+    // The partial sums are used by one call at a time, in stream order; a stream that is
+    // being captured cannot wait for another call's event, so captured calls do not split
+    j.split = 1;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool split = c.part.ptr && hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+    std::unique_lock<std::mutex> lock(c.part.mu, std::defer_lock);
+    if (split) {
+        lock.lock();
+        if (c.part.recorded) FBP_TRY_HIP(hipStreamWaitEvent(s, c.part.free_ev, 0));
+        j.split = c.part.planes;
+        j.part = c.part.ptr;
+    }
+    hipError_t e = c.rot ? launch_cone_rot(j, s) : launch_cone_bp(j, c.staged, s);
+    if (e == hipSuccess && split) {
+        e = launch_combine_parts(j.part, vol, 1, j.split, (size_t)c.Nz * c.N * c.N, j.scale, s);
+        if (e != hipSuccess) {
+            const int rc = hip_status(e, "partial-sum kernel launch");
+            return fail_after_queued(rc, c.part.free_ev, &c.part.recorded, s);
+        }
+        FBP_TRY_HIP(hipEventRecord(c.part.free_ev, s));
+        c.part.recorded = true;
+    }
+    if (e == hipSuccess && c.rot && (c.N & 1)) e = launch_cone_centre(j, s);
     return e == hipErrorInvalidValue ? FBP_EUNSUPPORTED : hip_status(e, "cone-beam backprojection launch");
 }
 
