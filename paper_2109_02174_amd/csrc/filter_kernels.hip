@@ -33,6 +33,8 @@
 //               8-tap fragment is one aligned 16-byte read.
 #include "fbp_internal.hpp"
 
+#include <type_traits>
+
 namespace fbp {
 
 namespace {
@@ -483,24 +485,31 @@ __device__ __forceinline__ void gemm_tile_split(const GemmJob& job, int mt, int 
         // the tap copies' slices, 16 bytes at a time (the table's rows start at y = -split_off)
         const int z0 = job.split_off - (nh0 + HN), units = cstride >> 3;
         const unsigned short* __restrict__ tab = static_cast<const unsigned short*>(job.split) + z0;
-        constexpr int U = 4;                                   // 16-byte pieces in flight per thread
         const int total = (FULL ? 48 : 24) * units;
         const float inv = 1.0f / (float)units;
-        for (int o0 = tid; o0 < total; o0 += U * NT) {
-            uint4 v[U];
-            int dst[U];
+        // U pieces in flight per thread: as many as there are, up to the registers
+        auto copies = [&](auto pieces) {
+            constexpr int U = decltype(pieces)::value;
+            for (int o0 = tid; o0 < total; o0 += U * NT) {
+                uint4 v[U];
+                int dst[U];
 #pragma unroll
-            for (int i = 0; i < U; ++i) {
-                const int o = min(o0 + i * NT, total - 1);     // no branch: all loads before the first wait
-                // o / units (exact: o < 2^16, and (o + 1/2) / units is at least 1 / (2 units) from an integer)
-                const int copy = (int)(((float)o + 0.5f) * inv), u = o - copy * units;
-                dst[i] = copy * cstride + 8 * u;
-                v[i] = *reinterpret_cast<const uint4*>(tab + (size_t)copy * job.split_len + 8 * u);
+                for (int i = 0; i < U; ++i) {
+                    const int o = min(o0 + i * NT, total - 1); // no branch: all loads before the first wait
+                    // o / units (exact: o < 2^16, and (o + 1/2) / units is at least 1 / (2 units) from an integer)
+                    const int copy = (int)(((float)o + 0.5f) * inv), u = o - copy * units;
+                    dst[i] = copy * cstride + 8 * u;
+                    v[i] = *reinterpret_cast<const uint4*>(tab + (size_t)copy * job.split_len + 8 * u);
+                }
+#pragma unroll
+                for (int i = 0; i < U; ++i)
+                    if (o0 + i * NT < total) *reinterpret_cast<uint4*>(Tc + dst[i]) = v[i];
             }
-#pragma unroll
-            for (int i = 0; i < U; ++i)
-                if (o0 + i * NT < total) *reinterpret_cast<uint4*>(Tc + dst[i]) = v[i];
-        }
+        };
+        if (MB == 2) copies(std::integral_constant<int, 4>{});
+        else if (total <= 2 * NT) copies(std::integral_constant<int, 2>{});
+        else if (total <= 4 * NT) copies(std::integral_constant<int, 4>{});
+        else copies(std::integral_constant<int, 10>{});
     }
 
     v4f big[MB][J], small[MB][J];

@@ -21,9 +21,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kind", ["ramlak", "hann"])
 @pytest.mark.parametrize("K,D,B", [
-    (1, 1, 1), (2, 2, 1), (3, 63, 1), (16, 64, 1), (17, 65, 1), (31, 127, 1), (32, 129, 1), (15, 384, 1),
-    (100, 385, 1), (300, 383, 30), (333, 769, 13),       # tall tiles, ragged rows and bins
-    (4, 2039, 1), (4, 2041, 1), (3, 4100, 1), (3, 5400, 1),   # longest detectors (even taps; odd taps only; past both)
+    (511, 200, 1), (512, 200, 1),        # both sides of the angle count that takes these kernels
+    (512, 1, 1), (513, 2, 1), (512, 63, 1), (528, 64, 1), (529, 65, 1), (543, 127, 1), (544, 129, 1), (527, 384, 1),
+    (512, 385, 1), (600, 383, 30), (1001, 769, 13),      # tall tiles, ragged rows and bins
+    (512, 2039, 1), (512, 2041, 1), (512, 4100, 1), (512, 5400, 1),   # longest detectors (even taps; odd taps only; past both)
 ])
 def test_split_filter_matches_oracle(kind, K, D, B):
     g = fbp.Geometry(K, D, 16, 1.0, filter=kind)
@@ -31,13 +32,14 @@ def test_split_filter_matches_oracle(kind, K, D, B):
     P[0, 0] *= 2.0 ** 40                                 # rows of very different size in one tile
     P[-1, -1] *= 2.0 ** -40
     got = fbp.fbp_filter(g, torch.tensor(P, device="cuda")).cpu().numpy()
+    rows = np.unique(np.concatenate([np.arange(18), np.arange(K - 18, K), np.arange(0, K, 37)]))
     for b in {0, B // 2, B - 1}:
-        ref = oracle.filter_rows(P[b:b + 1].astype(np.float64), 1.0, kind)[0]
-        bound = D * 2.0 ** -24 * np.max(np.abs(P[b]), axis=-1, keepdims=True) / 2 * 4
-        assert np.all(np.abs(got[b] - ref) <= bound), b
+        ref = oracle.filter_rows(P[b:b + 1, rows].astype(np.float64), 1.0, kind)[0]
+        bound = D * 2.0 ** -24 * np.max(np.abs(P[b, rows]), axis=-1, keepdims=True) / 2 * 4
+        assert np.all(np.abs(got[b, rows] - ref) <= bound), b
 
 
-@pytest.mark.parametrize("K,D,B", [(48, 101, 1), (200, 400, 20)])
+@pytest.mark.parametrize("K,D,B", [(512, 101, 1), (600, 400, 20)])
 def test_split_filter_with_column_weights(K, D, B):
     R = 500.0
     g = fbp.Geometry(K, D, 16, 1.0, source_distance=R)
@@ -52,7 +54,7 @@ def test_split_filter_with_column_weights(K, D, B):
 def test_large_and_non_finite_inputs():
     """Values up to FLT_MAX stay finite where the sum is; a non-finite input makes its own
     bin and the bins of the other parity of its row non-finite, and no others."""
-    K, D = 40, 200
+    K, D = 512, 200
     g = fbp.Geometry(K, D, 16, 1.0)
     P = ph.rng_for(1902, 0).normal(size=(1, K, D)).astype(np.float32)
     clean = fbp.fbp_filter(g, torch.tensor(P, device="cuda")).cpu().numpy()
