@@ -63,7 +63,10 @@ __global__ __launch_bounds__(kFanThreads) void fan_bp_kernel(FanJob job) {
     const int kpart = (K + job.split - 1) / job.split;
     const int kbeg = job.split > 1 ? g * kpart : 0;
     const int kend = job.split > 1 ? min(K, kbeg + kpart) : K;
+    // slices g M .. g M + M - 1; a group past the end of the stack reads its last slice again
+    // and does not write it
     const float* __restrict__ qs = job.q + (job.split > 1 ? (size_t)0 : (size_t)g * M * qstride);
+    const int last = M == 1 ? 0 : min(M, job.n_slices - g * M) - 1;    // the group's last slice of the stack
     const float inv_wl = 1.0f / (float)WL;
     float acc[M];
 #pragma unroll
@@ -106,7 +109,7 @@ __global__ __launch_bounds__(kFanThreads) void fan_bp_kernel(FanJob job) {
 #pragma unroll
         for (int m = 0; m < M; ++m) {
             const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<float*>(qs + m * qstride + (size_t)k0 * D), (short)0, nk * D * 4, kRawF32);
+                const_cast<float*>(qs + min(m, last) * qstride + (size_t)k0 * D), (short)0, nk * D * 4, kRawF32);
 #pragma unroll 2
             for (int e = threadIdx.x; e < nk * WL; e += kFanThreads) {
                 const int kk = (int)(((float)e + 0.5f) * inv_wl), i = e - __mul24(kk, WL);
@@ -180,7 +183,8 @@ __global__ __launch_bounds__(kFanThreads) void fan_bp_kernel(FanJob job) {
         } else {
 #pragma unroll
             for (int m = 0; m < M; ++m)
-                job.img[((size_t)g * M + m) * N * N + (size_t)(r0 + dy) * N + (c0 + dx)] = acc[m] * job.scale;
+                if (m <= last)
+                    job.img[((size_t)g * M + m) * N * N + (size_t)(r0 + dy) * N + (c0 + dx)] = acc[m] * job.scale;
         }
     }
 }
@@ -224,7 +228,10 @@ __global__ __launch_bounds__(kFanThreads) void fan_rot_kernel(FanJob job) {
     const int kpart = (K4 + job.split - 1) / job.split;
     const int kbeg = job.split > 1 ? g * kpart : 0;
     const int kend = job.split > 1 ? min(K4, kbeg + kpart) : K4;
+    // slices g M .. g M + M - 1; a group past the end of the stack reads its last slice again
+    // and does not write it
     const float* __restrict__ qs = job.q + (job.split > 1 ? (size_t)0 : (size_t)g * M * qstride);
+    const int last = M == 1 ? 0 : min(M, job.n_slices - g * M) - 1;    // the group's last slice of the stack
     const float inv_wl = 1.0f / (float)WL;
     float acc[4][M];
 #pragma unroll
@@ -271,7 +278,7 @@ __global__ __launch_bounds__(kFanThreads) void fan_rot_kernel(FanJob job) {
             __amdgpu_buffer_rsrc_t rows[M];
 #pragma unroll
             for (int mm = 0; mm < M; ++mm)
-                rows[mm] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(qs + mm * qstride), (short)0,
+                rows[mm] = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(qs + min(mm, last) * qstride), (short)0,
                                                              (int)(qstride * 4), kRawF32);
             for (int e4 = threadIdx.x; e4 < 4 * nk * WL; e4 += kFanThreads) {
                 const int km = (int)(((float)e4 + 0.5f) * inv_wl);
@@ -350,7 +357,8 @@ __global__ __launch_bounds__(kFanThreads) void fan_rot_kernel(FanJob job) {
                 job.part[(size_t)g * N * N + pix] = acc[j][0];
             } else {
 #pragma unroll
-                for (int mm = 0; mm < M; ++mm) job.img[((size_t)g * M + mm) * N * N + pix] = acc[j][mm] * job.scale;
+                for (int mm = 0; mm < M; ++mm)
+                    if (mm <= last) job.img[((size_t)g * M + mm) * N * N + pix] = acc[j][mm] * job.scale;
             }
         }
     }
@@ -360,6 +368,7 @@ __global__ __launch_bounds__(kFanThreads) void fan_rot_kernel(FanJob job) {
         const size_t pix = (size_t)(N >> 1) * N + (N >> 1);
 #pragma unroll
         for (int mm = 0; mm < M; ++mm) {
+            if (mm > last) continue;
             const float* __restrict__ qm = qs + mm * qstride;
             float csum = 0.0f;
             for (int t = lane; t < nv; t += 64) {     // view kbeg + t / 4 + (t % 4) K4
@@ -395,8 +404,8 @@ size_t fan_rot_lds_bytes(int KB, int WL, int M) {
 }
 
 // Quarter-turn form (N >= 2, K = 4 K4 with the views in quarter turns, K D 4 bytes
-// addressable by a buffer resource): groups of M slices, the rest one slice per
-// workgroup; a single slice may split its base views over job.split parts.
+// addressable by a buffer resource): groups of M slices (the last one may be short);
+// a single slice may split its base views over job.split parts.
 hipError_t launch_fan_rot(const FanJob& job, int n_slices, int M, int KBm, hipStream_t stream) {
     if (n_slices <= 0) return hipSuccess;
     if (job.N < 2 || (job.K & 3) || job.K < 4 || job.KB < 1 || 4 * job.KB > kFanThreads || job.WL < 2 ||
@@ -404,33 +413,21 @@ hipError_t launch_fan_rot(const FanJob& job, int n_slices, int M, int KBm, hipSt
         !fan_rot_addressable(job.K, job.D, job.WL) || job.tiles_x != ((job.N + 1) / 2 + kFanTile - 1) / kFanTile)
         return hipErrorInvalidValue;
     const int64_t tiles = (int64_t)job.tiles_x * ((job.N / 2 + kFanTile - 1) / kFanTile);
-    const int grouped = (M > 1) ? n_slices - n_slices % M : 0;
-    if (grouped > 0) {
-        FanJob j = job;
+    FanJob j = job;
+    j.n_slices = n_slices;
+    if (M > 1) {
         j.KB = KBm;
         j.split = 1;
         const size_t lds = fan_rot_lds_bytes(KBm, job.WL, M);
-        const int64_t blocks = tiles * (grouped / M);
+        const int64_t blocks = tiles * ((n_slices + M - 1) / M);
         if (blocks > INT32_MAX || lds > kFanLdsBudget) return hipErrorInvalidValue;
-        const hipError_t e = (M == 2)
-            ? launch_kernel(fan_rot_kernel<2>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j)
-            : launch_kernel(fan_rot_kernel<4>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j);
-        if (e != hipSuccess) return e;
+        return (M == 2) ? launch_kernel(fan_rot_kernel<2>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j)
+                        : launch_kernel(fan_rot_kernel<4>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j);
     }
-    const int rest = n_slices - grouped;
-    if (rest == 0) return hipSuccess;
     const size_t lds = fan_rot_lds_bytes(job.KB, job.WL, 1);
     if (lds > kFanLdsBudget) return hipErrorInvalidValue;
-    if (job.split > 1) {                                               // one slice, base views split over parts
-        if (n_slices != 1 || M != 1 || !job.part || job.split > job.K / 4) return hipErrorInvalidValue;
-        const int64_t blocks = tiles * job.split;
-        if (blocks > INT32_MAX) return hipErrorInvalidValue;
-        return launch_kernel(fan_rot_kernel<1>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, job);
-    }
-    FanJob j = job;
-    j.q = job.q + (size_t)grouped * job.K * job.D;
-    j.img = job.img + (size_t)grouped * job.N * job.N;
-    const int64_t blocks = tiles * rest;
+    if (job.split > 1 && (n_slices != 1 || !job.part || job.split > job.K / 4)) return hipErrorInvalidValue;
+    const int64_t blocks = tiles * (job.split > 1 ? job.split : n_slices);   // one slice may split its base views over parts
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
     return launch_kernel(fan_rot_kernel<1>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j);
 }
@@ -442,40 +439,26 @@ hipError_t launch_preweight(const float* in, float* out, const float* w, int64_t
     return launch_kernel(preweight_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, in, out, w, n, D);
 }
 
-// n_slices of one geometry: groups of M through the M-slice kernel (KB views per
-// block for it), the rest one slice per workgroup.
+// n_slices of one geometry: groups of M through the M-slice kernel (KBm views per block
+// for it; the last group may be short); a single slice may split its views over parts.
 hipError_t launch_fan_bp(const FanJob& job, int n_slices, int M, int KBm, hipStream_t stream) {
     if (n_slices <= 0) return hipSuccess;
     if (job.KB < 1 || job.WL < 2 || (M != 1 && M != 2 && M != 4) || (M > 1 && KBm < 1)) return hipErrorInvalidValue;
     const int64_t tiles = (int64_t)job.tiles_x * job.tiles_x;
-    const int grouped = (M > 1) ? n_slices - n_slices % M : 0;
-    if (grouped > 0) {
-        FanJob j = job;
-        j.KB = KBm;
-        const size_t lds = fan_lds_bytes(KBm, job.WL, M);
-        const int64_t blocks = tiles * (grouped / M);
-        if (blocks > INT32_MAX || lds > kFanLdsBudget) return hipErrorInvalidValue;
-        const hipError_t e = (M == 2)
-            ? launch_kernel(fan_bp_kernel<2>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j)
-            : launch_kernel(fan_bp_kernel<4>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j);
-        if (e != hipSuccess) return e;
-    }
-    const int rest = n_slices - grouped;
-    if (rest == 0) return hipSuccess;
-    if (job.split > 1) {                                               // one slice, views split over parts
-        if (n_slices != 1 || M != 1 || !job.part || job.split > job.K) return hipErrorInvalidValue;
-        const size_t lds = fan_lds_bytes(job.KB, job.WL, 1);
-        const int64_t blocks = tiles * job.split;
-        if (blocks > INT32_MAX || lds > kFanLdsBudget) return hipErrorInvalidValue;
-        return launch_kernel(fan_bp_kernel<1>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, job);
-    }
     FanJob j = job;
-    j.q = job.q + (size_t)grouped * job.K * job.D;
-    j.img = job.img + (size_t)grouped * job.N * job.N;
-    const size_t lds = fan_lds_bytes(job.KB, job.WL, 1);
-    const int64_t blocks = tiles * rest;
+    j.n_slices = n_slices;
+    if (M > 1) {
+        j.KB = KBm;
+        j.split = 1;
+    }
+    if (j.split > 1 && (n_slices != 1 || !j.part || j.split > j.K)) return hipErrorInvalidValue;
+    const size_t lds = fan_lds_bytes(j.KB, j.WL, M);
+    const int64_t blocks = tiles * (j.split > 1 ? j.split : (n_slices + M - 1) / M);
     if (blocks > INT32_MAX || lds > kFanLdsBudget) return hipErrorInvalidValue;
-    return launch_kernel(fan_bp_kernel<1>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j);
+    const dim3 grid((unsigned)blocks), block(kFanThreads);
+    return M == 1   ? launch_kernel(fan_bp_kernel<1>, grid, block, lds, stream, j)
+           : M == 2 ? launch_kernel(fan_bp_kernel<2>, grid, block, lds, stream, j)
+                    : launch_kernel(fan_bp_kernel<4>, grid, block, lds, stream, j);
 }
 
 }  // namespace fbp

@@ -305,12 +305,12 @@ struct FanJob {
     float scale;          // 2 pi / K
     float* part;          // split > 1: [split][N][N] partial sums (one slice, M = 1)
     int32_t split;        // view parts of a single slice (1: none)
+    int32_t n_slices;     // slices of the stack (set by the launch)
 };
 constexpr int kFanTile = 16;
 constexpr size_t kFanLdsBudget = 48 * 1024;
 size_t fan_lds_bytes(int KB, int WL, int M);
-// n_slices through the M-slice kernel (M = 2 or 4, KBm views per block) in groups,
-// the remainder (and everything when M = 1) one slice per workgroup.
+// n_slices in groups of M (1, 2 or 4; KBm views per block of a group).
 hipError_t launch_fan_bp(const FanJob& job, int n_slices, int M, int KBm, hipStream_t stream);
 // Quarter-turn form (N >= 2; K = 4 K4 with view k + i K4 at angle b_k + i pi/2):
 // a workgroup owns a tile of the base region, rows [0, N/2) by columns [0, (N+1)/2)

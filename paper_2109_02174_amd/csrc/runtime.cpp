@@ -185,10 +185,10 @@ struct Plan {
     double R = 0.0;
     double* d_fcs = nullptr;
     float* d_fanw = nullptr;
-    int fan_WL = 0, fan_KB = 0, fan_KB4 = 0;   // window pairs; views per block (one slice, four)
+    int fan_WL = 0, fan_KB = 0, fan_KB2 = 0, fan_KB4 = 0;   // window pairs; views per block (one slice, two, four)
     int fan_split = 1;                          // view parts of a single slice
     bool fan_rot = false;                       // quarter-turn form (a quadrant tile and its turns)
-    int fan_rot_KB = 0, fan_rot_M = 1, fan_rot_KBm = 0;   // its base views per block; stack group
+    int fan_rot_KB = 0, fan_rot_KB2 = 0, fan_rot_KB4 = 0;   // its base views per block: one slice, groups of two and four (0: none)
     double fan_half_span = 0.0;
     // FFT filter path: twiddles and the taps' DFT for L = 2^fft_log2 (made on first use)
     float2* d_fft_tw = nullptr;
@@ -263,12 +263,23 @@ bool quarter_turn_symmetric(const std::vector<double>& angles) {
 // Quarter-turn fan beam: LDS per workgroup for the staged windows of one slice
 // (small blocks: more workgroups per CU hide the staging and barrier latency; 20 KB
 // measured best of 16-48 KB at 512^2 / 720 views) and of a stack group (40 KB: two
-// base views of four slices), workgroups per CU a single slice's base-view split
-// aims at, stack groups tried (largest first).
+// base views of four slices), and workgroups per CU a single slice's base-view split
+// aims at.
 constexpr size_t kFanRotLds = 20 * 1024;
 constexpr size_t kFanRotLdsStack = 40 * 1024;
 constexpr int kFanRotWgsPerCu = 8;
-constexpr int kFanRotStackM[] = {4, 2};
+// Time of a stack in groups of M slices, per (base) view and relative, from g, the
+// workgroups per CU: a floor (one workgroup's serial walk) and growth, for quarter-turn
+// groups of two with a step where more than the four that fit a CU at once are needed.
+// Fitted to stacks of 4 to 16 slices of 128^2 to 700^2: groups of four make each pixel's
+// maps for four slices, groups of two leave twice the workgroups to hide their blocks'
+// latency.  Two take 0.35-0.75x the time of four below two workgroups of four per CU,
+// 0.95-1.05x at three, 1.05-1.3x from four on.
+double fan_stack_time(bool rot, int M, double g) {
+    if (!rot) return M == 2 ? std::max(0.185, 0.045 + 0.0465 * g) : std::max(0.26, 0.15 + 0.064 * g);
+    if (M == 4) return g <= 4.0 ? 1.9 * std::max(1.0, 0.82 + 0.165 * g) : 0.7 * g;
+    return g <= 4.0 ? 1.05 * std::max(1.0, 0.62 + 0.21 * g) : g <= 8.0 ? 2.1 + 0.22 * (g - 4.0) : 0.375 * g;
+}
 
 // Fan-beam views in quarter turns: K = 4 K4 and b_{k + i K4} = b_k + i pi/2 (mod 2 pi)
 // for every k < K4 and i = 1..3.
@@ -508,6 +519,7 @@ int make_fan_plan(Plan* p) {
     p->fan_WL = (int)std::ceil(2.0 * p->fan_half_span) + 4;
     p->fan_KB = (int)std::min<size_t>(64, (kFanLdsBudget - 64 * 36) / (8 * (size_t)p->fan_WL));
     if (p->fan_KB < 1) return FBP_EUNSUPPORTED;
+    p->fan_KB2 = (int)std::min<size_t>(16, (kFanLdsBudget - 64 * 36) / (2 * 8 * (size_t)p->fan_WL));
     p->fan_KB4 = (int)std::min<size_t>(16, (kFanLdsBudget - 64 * 36) / (4 * 8 * (size_t)p->fan_WL));
     // quarter-turn form when the views come in quarter turns (N >= 2): base views
     // per block for one slice, and the largest stack group whose block fits
@@ -515,13 +527,9 @@ int make_fan_plan(Plan* p) {
     if (p->fan_rot) {
         p->fan_rot_KB = (int)std::min<size_t>(64, kFanRotLds / fan_rot_lds_bytes(1, p->fan_WL, 1));
         p->fan_rot = p->fan_rot_KB >= 1;
-        for (int m : kFanRotStackM) {
+        for (int m : {2, 4}) {
             const int kb = (int)std::min<size_t>(64, kFanRotLdsStack / fan_rot_lds_bytes(1, p->fan_WL, m));
-            if (kb >= 2) {
-                p->fan_rot_M = m;
-                p->fan_rot_KBm = kb;
-                break;
-            }
+            if (kb >= 2) (m == 2 ? p->fan_rot_KB2 : p->fan_rot_KB4) = kb;
         }
     }
     // single slices: views (base views) split over enough parts for about 16
@@ -1178,11 +1186,17 @@ int run_fan_backproject(Plan& p, int32_t n, const float* filt, float* img, hipSt
     j.split = 1;
     if (p.fan_rot) j.KB = p.fan_rot_KB;
     auto launch = [&](const FanJob& jj, int ns, int m) {
-        return p.fan_rot ? launch_fan_rot(jj, ns, m, p.fan_rot_KBm, s) : launch_fan_bp(jj, ns, m, p.fan_KB4, s);
+        return p.fan_rot ? launch_fan_rot(jj, ns, m, m == 4 ? p.fan_rot_KB4 : p.fan_rot_KB2, s)
+                         : launch_fan_bp(jj, ns, m, m == 4 ? p.fan_KB4 : p.fan_KB2, s);
     };
     // stacks of 4 or more share each pixel's map over several slices per workgroup
-    const int M = p.fan_rot ? ((n >= kStackMinSlices && p.fan_rot_KBm >= 1) ? p.fan_rot_M : 1)
-                            : ((n >= kStackMinSlices && p.fan_KB4 >= 1) ? 4 : 1);
+    int M = 1;
+    if (n >= kStackMinSlices) {
+        const int kb2 = p.fan_rot ? p.fan_rot_KB2 : p.fan_KB2, kb4 = p.fan_rot ? p.fan_rot_KB4 : p.fan_KB4;
+        const double tiles = (double)j.tiles_x * (p.fan_rot ? (p.N / 2 + kFanTile - 1) / kFanTile : j.tiles_x);
+        auto time = [&](int m) { return fan_stack_time(p.fan_rot, m, tiles * ((n + m - 1) / m) / cu_count(p.device)); };
+        M = kb4 >= 1 && (kb2 < 1 || time(4) < time(2)) ? 4 : kb2 >= 1 ? 2 : 1;
+    }
     if (M == 1 && p.fan_split > 1 && p.part.ptr) {
         // slice by slice, the views split over parts summed in a fixed order
         PartBuffer& pb = p.part;
