@@ -1225,11 +1225,15 @@ int run_fan_backproject(Plan& p, int32_t n, const float* filt, float* img, hipSt
 }
 
 // n slices of a stack with shape sh: groups of sh.multi slices per workgroup, the
-// rest one slice per workgroup; both give bitwise the same slices.
+// rest one slice per workgroup; both give bitwise the same slices.  Groups only where they
+// are more than the CUs: fewer leave CUs idle and each a longer walk (64^2 to 300^2, 4 to 16
+// slices: one slice per workgroup 0.6-0.95x the time up to 0.85 groups per CU, equal at one,
+// 1.05-1.2x from 1.5 on).
 int run_stack(const Plan& p, const ShapeParams& sh, int32_t n, const float* filt, float* img, hipStream_t s) {
     const int tiles = sh.tiles_x * sh.tiles_y;
     const size_t qs = (size_t)p.K * p.D, is = (size_t)p.N * p.N;
-    const int32_t grouped = (sh.multi > 1) ? n - n % sh.multi : 0;
+    const bool groups = sh.multi > 1 && 4 * (int64_t)(n / sh.multi) * tiles >= 5 * (int64_t)cu_count(p.device);
+    const int32_t grouped = groups ? n - n % sh.multi : 0;
     if (grouped > 0) {
         if ((int64_t)(grouped / sh.multi) * tiles > INT32_MAX) return FBP_EUNSUPPORTED;
         const BpJob j = bp_job(p, sh, filt, img, true);
