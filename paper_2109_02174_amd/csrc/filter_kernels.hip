@@ -933,7 +933,10 @@ hipError_t launch_gemm_split(const GemmJob& job, hipStream_t stream) {
     auto blocks = [&](const SplitShape& sh) {
         return (int64_t)((job.R + sh.rows() - 1) / sh.rows()) * ((job.Dh + sh.hn() - 1) / sh.hn());
     };
-    if (2 * blocks(kSplitTall) >= cus) return launch_split<kSplitTall.mb, kSplitTall.j, kSplitTall.wc>(job, stream);
+    // tall tiles where they give half the CUs work, unless a short detector leaves most of
+    // their 192 bins a parity empty (100 bins, 34000 rows: 21 us tall, 15 us small)
+    auto width = [&](const SplitShape& sh) { return (job.Dh + sh.hn() - 1) / sh.hn() * sh.hn(); };
+    if (2 * blocks(kSplitTall) >= cus && width(kSplitTall) <= 2 * width(kSplitSmall)) return launch_split<kSplitTall.mb, kSplitTall.j, kSplitTall.wc>(job, stream);
     if (4 * blocks(kSplitSmall) >= cus) return launch_split<kSplitSmall.mb, kSplitSmall.j, kSplitSmall.wc>(job, stream);
     return launch_split<kSplitTiny.mb, kSplitTiny.j, kSplitTiny.wc>(job, stream);
 }

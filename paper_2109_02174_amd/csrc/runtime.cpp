@@ -1041,12 +1041,14 @@ int ensure_taps(Plan* p, int prec) {
 
 // ------------------------------------------------------------------ launch helpers
 
-// Geometries whose FP32 rows go through the split kernels: those with this many angles.
+// Geometries whose FP32 rows go through the split kernels: those with this many angles and
+// bins (60 bins 1.4x the time, 100 to 183 bins 0.85-1.14x, from 255 on 0.69-0.97x).
 // With fewer, a single slice's rows are a handful of tiles, each a serial walk over the
 // detector that the split's larger tap tables and longer MFMA chains lengthen (62 to 400
 // angles: reconstruction of one slice 1.0-1.15x the time, from 512 angles on 0.98-1.0x, 64
 // slices 0.93x).  By the geometry alone, so that a slice gets the same bits in any call.
-constexpr int kSplitAngles = 512;
+constexpr int kSplitAngles = 512, kSplitBins = 192;
+bool split_rows(const Plan& p) { return p.K >= kSplitAngles && p.D >= kSplitBins; }
 
 GemmJob gemm_job(const Plan& p, int prec, const float* sino, float* filt, int rows, bool split) {
     GemmJob j{};
@@ -1126,7 +1128,7 @@ hipError_t launch_filter_rows(const Plan& p, int prec, const float* in, float* o
         j.colw = colw;
         return launch_fft_filter(j, s);
     }
-    GemmJob j = gemm_job(p, prec, in, out, rows, p.K >= kSplitAngles);
+    GemmJob j = gemm_job(p, prec, in, out, rows, split_rows(p));
     j.colw = colw;
     if (j.split) return launch_gemm_split(j, s);
     if (prec == kFP32) {
@@ -1559,7 +1561,7 @@ int reconstruct_batch_parallel(const fbp_job* jobs, int32_t n, const BatchLayout
             gp[pre_g] = 0;
             for (int32_t i = 0; i < n; ++i) {
                 const Plan& p = *plans[(size_t)i];
-                const bool full = p.filter != FBP_FILTER_RAMLAK, split = prec == kFP32 && p.d_split && p.K >= kSplitAngles;
+                const bool full = p.filter != FBP_FILTER_RAMLAK, split = prec == kFP32 && p.d_split && split_rows(p);
                 if (full != ((kind & 1) != 0) || split != (kind >= 2)) continue;
                 gj[pos_g] = gemm_job(p, prec, jobs[i].sino, qptr[(size_t)i], p.K, split);
                 if (split) {

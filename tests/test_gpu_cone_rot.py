@@ -90,3 +90,15 @@ def test_split_views_of_small_volumes(K, N):
         graph.replay()
         torch.cuda.synchronize()
         assert np.max(np.abs(out.cpu().numpy() - ref[rep])) <= 2.0 * _tol(Q[rep], N, Nz, 1.0, R), rep
+
+
+@pytest.mark.parametrize("K,Dv,Du", [(5, 7, 1), (3, 11, 63), (40, 64, 100), (30, 90, 190), (4, 33, 385)])
+def test_cone_filter_of_short_detectors_matches_oracle(K, Dv, Du):
+    """The detector rows of a cone go through the split filter whatever their length: short
+    detectors in small tiles, also where the rows are many."""
+    R, du, dv = 700.0, 1.0, 1.2
+    g = fbp.ConeGeometry(K, Du, Dv, 16, 8, R, du, dv)
+    P = ph.rng_for(1813, K + Du).normal(size=(K, Dv, Du)).astype(np.float32)
+    got = fbp.fbp_cone_filter(g, torch.tensor(P, device="cuda")).cpu().numpy()
+    ref = oracle.cone_filter(P.astype(np.float64), du, dv, R, "ramlak")
+    assert np.max(np.abs(got - ref)) <= Du * 2.0 ** -24 * np.max(np.abs(P)) / (4 * du) * 4

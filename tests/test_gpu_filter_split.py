@@ -21,8 +21,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kind", ["ramlak", "hann"])
 @pytest.mark.parametrize("K,D,B", [
-    (511, 200, 1), (512, 200, 1),        # both sides of the angle count that takes these kernels
-    (512, 1, 1), (513, 2, 1), (512, 63, 1), (528, 64, 1), (529, 65, 1), (543, 127, 1), (544, 129, 1), (527, 384, 1),
+    (511, 200, 1), (512, 200, 1), (512, 191, 1), (512, 192, 1),   # both sides of the sizes that take these kernels
+    (512, 1, 1), (513, 255, 1), (528, 256, 1), (529, 257, 1), (543, 383, 1), (544, 384, 30), (527, 385, 1),
     (512, 385, 1), (600, 383, 30), (1001, 769, 13),      # tall tiles, ragged rows and bins
     (512, 2039, 1), (512, 2041, 1), (512, 4100, 1), (512, 5400, 1),   # longest detectors (even taps; odd taps only; past both)
 ])
@@ -39,7 +39,7 @@ def test_split_filter_matches_oracle(kind, K, D, B):
         assert np.all(np.abs(got[b, rows] - ref) <= bound), b
 
 
-@pytest.mark.parametrize("K,D,B", [(512, 101, 1), (600, 400, 20)])
+@pytest.mark.parametrize("K,D,B", [(512, 201, 1), (600, 400, 20)])
 def test_split_filter_with_column_weights(K, D, B):
     R = 500.0
     g = fbp.Geometry(K, D, 16, 1.0, source_distance=R)
