@@ -1002,7 +1002,12 @@ int ensure_taps(Plan* p, int prec) {
         (void)hipFree(dev);
         return hip_fail(e, "hipMemcpy (filter taps)");
     }
-    if (prec == kFP32 && gemm_split_fits(p->Dh, full)) {
+    // Not Shepp-Logan: its centre tap is three times its neighbours and is summed among them
+    // in one accumulator, so its images came out less exact than by the FP32 products
+    // (relative error against 64 bits over 11 geometries of 200 to 790 bins: 2.8e-7..9.5e-7
+    // by FP32 products, 1.04-1.6x that by the split; Ram-Lak, whose centre tap is added last,
+    // and Hann 0.4-1.16x, 0.8x in the mean).
+    if (prec == kFP32 && p->filter != FBP_FILTER_SHEPP_LOGAN && gemm_split_fits(p->Dh, full)) {
         // each tap as a sum of three bf16 numbers, in eight copies shifted by one element
         const int off = gemm_split_off(p->Dh), zlen = gemm_split_len(p->Dh);
         const int tables = full ? 2 : 1;

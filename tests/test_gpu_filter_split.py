@@ -51,6 +51,16 @@ def test_split_filter_with_column_weights(K, D, B):
     assert np.max(np.abs(got[-1] - ref)) <= D * 2.0 ** -24 * np.max(np.abs(P)) / 4 * 4
 
 
+@pytest.mark.parametrize("K,D", [(512, 192), (600, 534)])
+def test_shepp_logan_stays_on_fp32_products(K, D):
+    """The same rows in a geometry of too few angles for the bf16 products: the same bits."""
+    P = ph.rng_for(1903, K).normal(size=(1, K, D)).astype(np.float32)
+    few = 128
+    want = fbp.fbp_filter(fbp.Geometry(few, D, 16, 1.0, filter="shepp-logan"), torch.tensor(P[:, :few], device="cuda"))
+    got = fbp.fbp_filter(fbp.Geometry(K, D, 16, 1.0, filter="shepp-logan"), torch.tensor(P, device="cuda"))
+    assert torch.equal(got[:, :few], want)
+
+
 def test_large_and_non_finite_inputs():
     """Values up to FLT_MAX stay finite where the sum is; a non-finite input makes its own
     bin and the bins of the other parity of its row non-finite, and no others."""
