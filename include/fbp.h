@@ -50,7 +50,10 @@
  * reconstructed alone, in a stack or inside a batch gives bitwise-equal images,
  * whatever the autotuner chose.  Other geometries may run single slices, stacks
  * and batches with different tile shapes (and the autotuner picks shapes by
- * timing); those paths agree within the FP32 tolerance.
+ * timing); those paths agree within the FP32 tolerance.  Cone-beam volumes of few
+ * workgroups split their views over partial volumes that are added in a fixed
+ * order; a call on a capturing stream does not split them, so its voxels agree
+ * with the eager call's within the FP32 tolerance.
  */
 #ifndef FBP_H
 #define FBP_H
