@@ -410,10 +410,6 @@ struct GemmJob {
     int32_t nb;           // FP32 grid launches: tiles of 32 nb output bins (nb = 1, 2, 3; tiles_n =
                           // ceil(D / (32 nb))); 0 = the default 64-bin tiles
     int32_t groups;       // FP32 grid launches: 1 or 2 groups of four waves per tile (same bits)
-    const void* split;    // FP32: bf16 triples of the taps for the split kernels (null: detector too long),
-                          // [odd, even][3][8 copies][split_len]; copy c holds tap(-2 y - 1) (even: tap(-2 y))
-                          // of y = z + c - split_off at z
-    int32_t split_len, split_off;
 };
 static_assert(sizeof(GemmJob) % 8 == 0, "GemmJob layout");
 
@@ -421,13 +417,6 @@ constexpr int kGemmBM = 32;   // rows per GEMM tile
 constexpr int kGemmBN = 64;   // output bins per GEMM tile
 
 hipError_t launch_gemm_grid(int prec, const GemmJob& job, hipStream_t stream);
-
-// FP32 rows through bf16 matrix products (six of the nine products of bf16 triples), for
-// detectors whose tap copies fit a CU's LDS; the same bits for every grid and in lists.
-bool gemm_split_fits(int Dh, bool full);
-int gemm_split_off(int Dh);
-int gemm_split_len(int Dh);
-hipError_t launch_gemm_split(const GemmJob& job, hipStream_t stream);
 
 struct GemmListArgs {
     const GemmJob* jobs;        // device [n_jobs]
@@ -437,12 +426,6 @@ struct GemmListArgs {
 // `args` is a DEVICE pointer (the batch header in the workspace).
 hipError_t launch_gemm_list(int prec, bool full, const GemmListArgs* args, int grid, size_t lds_bytes,
                             hipStream_t stream);
-// Lists of split jobs (tiles_n and the prefix count gemm_split_tiles).
-int gemm_split_tiles(int R, int Dh);
-int gemm_split_tiles_n(int Dh);
-int gemm_split_lds_bytes(int Dh, bool full);
-int gemm_split_occupancy(bool full, size_t lds_bytes);
-hipError_t launch_gemm_split_list(bool full, const GemmListArgs* args, int grid, size_t lds_bytes, hipStream_t stream);
 // LDS of a filter workgroup; full: the kernel has even taps too (their copies
 // double the tap area); nb: FP32 tiles of 32 nb output bins (0: the default 64);
 // cpb: FP32 chunks staged per panel barrier (1 or 2).

@@ -24,16 +24,12 @@
 // while the current one is multiplied; the LDS panel they are staged into is
 // double-buffered, so each barrier step needs one barrier (FP32 two-group tiles
 // stage two chunks per step, the others one).
-//   FP32:       through bf16 products (below) where the tap copies fit the CU's LDS
-//               (detectors to about 4600 bins, kernels with even taps 2000); longer
-//               ones v_mfma_f32_16x16x4_f32, 32 inputs per parity per chunk.
+//   FP32:       v_mfma_f32_16x16x4_f32, 32 inputs per parity per chunk.
 //   BF16/FP16:  v_mfma_f32_16x16x32_{bf16,f16}, 64 per parity per chunk; the rows
 //               are rounded to 16 bits (RNE) as they are staged, and the tap slice
 //               is kept in LDS as eight copies shifted by one element so every
 //               8-tap fragment is one aligned 16-byte read.
 #include "fbp_internal.hpp"
-
-#include <type_traits>
 
 namespace fbp {
 
@@ -340,289 +336,6 @@ __device__ __forceinline__ void gemm_tile_f32(const GemmJob& job, int mt, int nt
     }
 }
 
-// ---------------------------------------------------------------- FP32 through bf16 matrix products
-//
-// FP32 rows and taps as sums of three bf16 numbers each (8 + 8 + 8 significant bits: the
-// first truncated, the others rounded, so every finite FP32 number splits exactly; the taps
-// come rounded from double).  Of the nine products the six of relative size 2^-16 and above
-// are taken, on v_mfma_f32_16x16x32_bf16 with FP32 accumulation; the three left out are
-// below 2^-24 of the term.  The leading products (x0 t0) and the five small ones have
-// accumulators of their own, added at the end.
-//
-// A tile is 16 MB rows x 16 J WC output bins of each parity, one wave per parity and 16 J
-// bins.  Rows are split once per tile as they are staged: a lane trades values with the
-// lane two columns on (same parity), so that splits and LDS stores work on pairs.  The
-// taps are staged as eight copies shifted by one element, so that a lane's eight taps are
-// one aligned 16-byte read; the copies lie 8 banks apart, which keeps the 16 lanes of a row
-// off each other's banks.  Chunks of 32 inputs per parity, double-buffered, one barrier per
-// chunk, the rows of the next chunks loading meanwhile.
-//
-// Every output adds the same products in the same order whatever the tile, so the tile
-// shape is free to follow the grid.
-//
-// Long grids are bound by the matrix cores and the LDS about equally: 46080 rows of 725 bins
-// (64 slices of 720 views) 284 -> 160 us (MFMA alone 65 us at the card's peak, the rows'
-// traffic about 50 us), against v_mfma_f32_16x16x4_f32 below at its issue rate.  One slice
-// (720 rows) takes as long either way, 8 us of latency: three to twelve chunks in turn.
-// Relative error against 64 bits there 5.8e-6 -> 3.6e-6 (most of it the ramp's cancelling
-// centre tap), Hann kernel 3.1e-6 -> 6.1e-7.  A non-finite input makes the outputs of the
-// other parity in its row NaN (and its own bin non-finite), where FP32 products may give
-// infinities; the rest of the row stays as it is.
-constexpr int kKS = 32;                   // inputs per parity per chunk
-constexpr int kASS = kKS + 8;             // LDS row stride (bf16): 16-byte rows
-__host__ __device__ constexpr int split_mpad(int Dh) { return (Dh + kKS - 1) / kKS * kKS; }
-// copies 16 elements = 8 banks apart (mod 64 banks)
-__host__ __device__ constexpr int copy_stride_split(int mpad, int hn) {
-    const int s = mpad + hn + 8;
-    return s + ((16 - s % 128) + 128) % 128;
-}
-
-// Chunks staged per barrier: two in the small eight-wave tiles, which are bound by the
-// latency of a step and not by its work.
-__host__ __device__ constexpr int split_cpb(int mb, int wc) { return mb == 1 && wc == 4 ? 2 : 1; }
-
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned pk_bf16(float a, float b) {
-    const v2bf v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(unsigned, v);
-}
-__device__ __forceinline__ void split3(float a, float b, unsigned (&out)[3]) {
-    const unsigned ua = __float_as_uint(a), ub = __float_as_uint(b);
-    out[0] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);       // high halves
-    float ra = a - __uint_as_float(ua & 0xFFFF0000u), rb = b - __uint_as_float(ub & 0xFFFF0000u);
-    out[1] = pk_bf16(ra, rb);
-    ra -= __uint_as_float(out[1] << 16);
-    rb -= __uint_as_float(out[1] & 0xFFFF0000u);
-    out[2] = pk_bf16(ra, rb);
-}
-
-// Epilogue: the centre tap meets the leading sum before the small one, so that what
-// cancels in the ramp cancels first (layout as in store_block).
-template <bool FULL>
-__device__ __forceinline__ void store_split(const v4f& big, const v4f& small, const float (&pre)[4], const GemmJob& job,
-                                            int row0, int nh0, int sg) {
-    const int l = threadIdx.x & 63;
-    const int n = 2 * (nh0 + (l & 15)) + sg;
-    if (n >= job.D) return;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int m = row0 + 4 * (l >> 4) + i;
-        if (m < job.R) {
-            const float v = (FULL ? big[i] : fmaf(job.diag, pre[i], big[i])) + small[i];
-            job.q[(size_t)m * job.D + n] = v * job.out_scale;
-        }
-    }
-}
-
-template <bool FULL, bool CW, int MB, int J, int WC>
-__device__ __forceinline__ void gemm_tile_split(const GemmJob& job, int mt, int nt, char* smem) {
-    constexpr int W = 2 * WC, NT = 64 * W;
-    constexpr int RM = 16 * MB, HN = 16 * J * WC;              // rows; output bins per parity
-    constexpr int EL = RM / W;                                 // rows of a chunk per wave
-    constexpr int CPB = split_cpb(MB, WC);                         // chunks staged per barrier
-    constexpr int PD = MB == 2 ? 3 : CPB == 1 ? 4 : 3 * CPB;   // chunks in flight (register ring)
-    static_assert(EL >= 2 && EL % 2 == 0, "row pairs");
-    constexpr int kPlane = RM * kASS, kBuf = 3 * 2 * kPlane;   // bf16 elements
-    unsigned short* As = reinterpret_cast<unsigned short*>(smem);   // [2 buffers][CPB][3][2 parities][RM][kASS]
-    unsigned short* Tc = As + 2 * CPB * kBuf;                  // [odd, even taps][3][8 copies][cstride]
-    const int tid = threadIdx.x, l = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int sg = w & 1, wc = w >> 1;                         // output parity, column range
-    const int m0 = mt * RM, nh0 = nt * HN;
-    const int R = job.R, D = job.D, Dh = job.Dh;
-    const int mpad = split_mpad(Dh), cstride = copy_stride_split(mpad, HN);
-    const int nch = mpad / kKS;
-    const __amdgpu_buffer_rsrc_t prow = tile_rows(job.p, m0, min(RM, R - m0), D);
-    const __amdgpu_buffer_rsrc_t wcol = col_weights(job);
-
-    float pf[PD][EL], pw[PD];
-    auto load = [&](int slot, int c) {                         // columns 64 c .. 64 c + 63, this wave's rows
-        const int col = c * 2 * kKS + l;
-        const int off = col < D ? col * 4 : kOutOfRange;
-#pragma unroll
-        for (int i = 0; i < EL; ++i) {
-            const int row = min(w * EL + i, R - 1 - m0);       // rows past the last: that one again (not stored)
-            pf[slot][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(prow, off, row * D * 4, 0));
-        }
-        if constexpr (CW) pw[slot] = load_weight(wcol, col);
-    };
-    const bool upper = (l & 2) != 0;
-    // lower lanes store the pair (c, c + 2) of the first row, upper ones (c - 2, c) of the second
-    const int a_st = (l & 1) * kPlane + (w * EL + (upper ? 1 : 0)) * kASS + ((l >> 2) << 1);
-    auto store = [&](int slot, unsigned short* Ab) {
-#pragma unroll
-        for (int i = 0; i < EL; i += 2) {
-            float x0 = pf[slot][i], x1 = pf[slot][i + 1];
-            if constexpr (CW) {
-                x0 *= pw[slot];
-                x1 *= pw[slot];
-            }
-            const float send = upper ? x0 : x1;
-            const float recv = __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, send), 0x4E, 0xF, 0xF, true));
-            unsigned v[3];
-            split3(upper ? recv : x0, upper ? x1 : recv, v);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) *reinterpret_cast<unsigned*>(Ab + q * 2 * kPlane + a_st + i * kASS) = v[q];
-        }
-    };
-#pragma unroll
-    for (int c = 0; c < PD - CPB; ++c) load(c, c);
-    // centre-tap inputs: with the first rows where registers allow (tall tiles: at the end)
-    constexpr bool kEarly = MB * J <= 2;
-    float pre[MB][J][4];
-    auto centre = [&]() {
-        if constexpr (!FULL) {
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-#pragma unroll
-                for (int j = 0; j < J; ++j)
-                    load_centre<CW>(pre[m][j], prow, wcol, D, 16 * m, nh0 + wc * 16 * J + 16 * j, sg);
-        }
-    };
-    if (kEarly) centre();
-    __syncthreads();                                           // LDS reuse across tiles of a persistent workgroup
-    {
-        // the tap copies' slices, 16 bytes at a time (the table's rows start at y = -split_off)
-        const int z0 = job.split_off - (nh0 + HN), units = cstride >> 3;
-        const unsigned short* __restrict__ tab = static_cast<const unsigned short*>(job.split) + z0;
-        const int total = (FULL ? 48 : 24) * units;
-        const float inv = 1.0f / (float)units;
-        // U pieces in flight per thread: as many as there are, up to the registers
-        auto copies = [&](auto pieces) {
-            constexpr int U = decltype(pieces)::value;
-            for (int o0 = tid; o0 < total; o0 += U * NT) {
-                uint4 v[U];
-                int dst[U];
-#pragma unroll
-                for (int i = 0; i < U; ++i) {
-                    const int o = min(o0 + i * NT, total - 1); // no branch: all loads before the first wait
-                    // o / units (exact: o < 2^16, and (o + 1/2) / units is at least 1 / (2 units) from an integer)
-                    const int copy = (int)(((float)o + 0.5f) * inv), u = o - copy * units;
-                    dst[i] = copy * cstride + 8 * u;
-                    v[i] = *reinterpret_cast<const uint4*>(tab + (size_t)copy * job.split_len + 8 * u);
-                }
-#pragma unroll
-                for (int i = 0; i < U; ++i)
-                    if (o0 + i * NT < total) *reinterpret_cast<uint4*>(Tc + dst[i]) = v[i];
-            }
-        };
-        if (MB == 2) copies(std::integral_constant<int, 4>{});
-        else if (total <= 2 * NT) copies(std::integral_constant<int, 2>{});
-        else if (total <= 4 * NT) copies(std::integral_constant<int, 4>{});
-        else copies(std::integral_constant<int, 10>{});
-    }
-
-    v4f big[MB][J], small[MB][J];
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int j = 0; j < J; ++j) big[m][j] = small[m][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    const int q = l >> 4;
-    const unsigned short* Ar = As + (1 - sg) * kPlane + (l & 15) * kASS + 8 * q;   // inputs of the other parity
-    const unsigned short* ArS = As + sg * kPlane + (l & 15) * kASS + 8 * q;        // same parity (FULL)
-    // y = m' - n' - s counted from the slice's first, -(nh0 + HN), at chunk 0 and block 0
-    const int yo = 8 * q - wc * 16 * J - (l & 15) - sg + HN, ye = yo + sg;
-    const unsigned short* Bo = Tc + (yo & 7) * cstride + (yo & ~7);
-    const unsigned short* Be = Tc + 24 * cstride + (ye & 7) * cstride + (ye & ~7);
-    auto product = [&](const unsigned short* a, const unsigned short* b) {
-        v8bf av[3][MB];
-#pragma unroll
-        for (int x = 0; x < 3; ++x)
-#pragma unroll
-            for (int m = 0; m < MB; ++m) av[x][m] = *reinterpret_cast<const v8bf*>(a + x * 2 * kPlane + m * 16 * kASS);
-        // JB blocks at a time, so that neighbouring MFMAs have different accumulators
-        constexpr int JB = MB == 1 ? J : 1;
-#pragma unroll
-        for (int j0 = 0; j0 < J; j0 += JB) {
-            v8bf bv[3][JB];
-#pragma unroll
-            for (int x = 0; x < 3; ++x)
-#pragma unroll
-                for (int j = 0; j < JB; ++j) bv[x][j] = *reinterpret_cast<const v8bf*>(b + x * 8 * cstride - 16 * (j0 + j));
-            auto mfma = [&](int x, int t, v4f (&acc)[MB][J]) {
-#pragma unroll
-                for (int j = 0; j < JB; ++j)
-#pragma unroll
-                    for (int m = 0; m < MB; ++m)
-                        acc[m][j0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[x][m], bv[t][j], acc[m][j0 + j], 0, 0, 0);
-            };
-            mfma(2, 0, small);
-            mfma(0, 0, big);
-            mfma(1, 1, small);
-            mfma(0, 2, small);
-            mfma(1, 0, small);
-            mfma(0, 1, small);
-        }
-    };
-    for (int cb = 0; cb < nch; cb += PD) {
-#pragma unroll
-        for (int u = 0; u < PD; u += CPB) {
-            const int c = cb + u;
-            // loads are issued unconditionally (past the end they read zeros), so that the
-            // wait before a chunk's store covers that chunk only
-#pragma unroll
-            for (int i = 0; i < CPB; ++i) load((u + PD - CPB + i) % PD, c + PD - CPB + i);
-            const int ab = ((c / CPB) & 1) * CPB * kBuf;       // double-buffered: one barrier per step
-#pragma unroll
-            for (int i = 0; i < CPB; ++i) store(u + i, As + ab + i * kBuf);
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < CPB; ++i) {
-                if (c + i < nch) {
-                    product(Ar + ab + i * kBuf, Bo + (c + i) * kKS);
-                    if constexpr (FULL) product(ArS + ab + i * kBuf, Be + (c + i) * kKS);
-                }
-            }
-        }
-    }
-    if (!kEarly) centre();
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-            store_split<FULL>(big[m][j], small[m][j], pre[m][j], job, m0 + 16 * m, nh0 + wc * 16 * J + 16 * j, sg);
-}
-
-// Tile shapes of the split kernels: row blocks per wave, 16-bin blocks per wave and parity,
-// column ranges.  Tall tiles split each row for 384 bins and share every tap fragment
-// between two row blocks; small ones fill the chip when there are few rows.
-struct SplitShape {
-    int mb, j, wc;
-    constexpr int rows() const { return 16 * mb; }
-    constexpr int hn() const { return 16 * j * wc; }
-    constexpr int threads() const { return 128 * wc; }
-};
-constexpr SplitShape kSplitTall{2, 3, 4}, kSplitSmall{1, 1, 4}, kSplitTiny{1, 1, 2};
-
-template <bool FULL, bool CW, int MB, int J, int WC>
-__global__ __launch_bounds__(128 * WC, MB == 2 ? 4 : 1) void gemm_split_kernel(GemmJob job) {
-    extern __shared__ float4 smem4[];
-    const int b = xcd_logical(blockIdx.x, gridDim.x);
-    const int mt = b / job.tiles_n, nt = b - mt * job.tiles_n;
-    gemm_tile_split<FULL, CW, MB, J, WC>(job, mt, nt, reinterpret_cast<char*>(smem4));
-}
-
-template <bool FULL>
-__global__ __launch_bounds__(128 * kSplitTall.wc, 4) void gemm_split_list_kernel(const GemmListArgs* __restrict__ args) {
-    extern __shared__ float4 smem4[];
-    const GemmListArgs a = load_const(args);
-    const auto* __restrict__ prefix = as_const(a.tile_prefix);
-    const int n_jobs = *as_const(a.counts);
-    if (n_jobs <= 0) return;
-    const int total = prefix[n_jobs];
-    for (int it = xcd_logical(blockIdx.x, gridDim.x); it < total; it += gridDim.x) {
-        int lo = 0, hi = n_jobs - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (prefix[mid] <= it) lo = mid; else hi = mid - 1;
-        }
-        const GemmJob job = load_const(a.jobs + lo);
-        const int tt = it - prefix[lo];
-        const int mt = tt / job.tiles_n, nt = tt - mt * job.tiles_n;
-        gemm_tile_split<FULL, false, kSplitTall.mb, kSplitTall.j, kSplitTall.wc>(job, mt, nt, reinterpret_cast<char*>(smem4));
-    }
-}
-
 // ---------------------------------------------------------------- 16-bit operands
 
 constexpr int kK16 = 64;                  // inputs per parity per chunk
@@ -880,65 +593,6 @@ hipError_t launch_f32_groups(const GemmJob& job, dim3 g, hipStream_t stream) {
         return launch_f32<NB, 2, 1>(job, g, (size_t)gemm_lds_bytes(kFP32, job.Dh, full, job.nb, 1), stream);
     }
     return launch_f32<NB, 1, 1>(job, g, (size_t)gemm_lds_bytes(kFP32, job.Dh, full, job.nb, 1), stream);
-}
-
-namespace {
-
-size_t split_lds(const SplitShape& sh, int Dh, bool full) {
-    return 2 * ((size_t)2 * split_cpb(sh.mb, sh.wc) * 3 * 2 * sh.rows() * kASS + (full ? 48 : 24) * (size_t)copy_stride_split(split_mpad(Dh), sh.hn()));
-}
-
-template <int MB, int J, int WC>
-hipError_t launch_split(GemmJob job, hipStream_t stream) {
-    constexpr SplitShape sh{MB, J, WC};
-    job.tiles_n = (job.Dh + sh.hn() - 1) / sh.hn();
-    const int64_t blocks = (int64_t)((job.R + sh.rows() - 1) / sh.rows()) * job.tiles_n;
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    const dim3 g((unsigned)blocks), b(sh.threads());
-    const size_t lds = split_lds(sh, job.Dh, job.full != 0);
-    if (job.full)
-        return job.colw ? launch_kernel(gemm_split_kernel<true, true, MB, J, WC>, g, b, lds, stream, job)
-                        : launch_kernel(gemm_split_kernel<true, false, MB, J, WC>, g, b, lds, stream, job);
-    return job.colw ? launch_kernel(gemm_split_kernel<false, true, MB, J, WC>, g, b, lds, stream, job)
-                    : launch_kernel(gemm_split_kernel<false, false, MB, J, WC>, g, b, lds, stream, job);
-}
-
-}  // namespace
-
-bool gemm_split_fits(int Dh, bool full) { return split_lds(kSplitTall, Dh, full) <= kMaxLdsBytes; }
-int gemm_split_off(int Dh) { return (Dh + 191) / 192 * 192; }
-int gemm_split_len(int Dh) { return gemm_split_off(Dh) + split_mpad(Dh) + 136; }
-int gemm_split_tiles(int R, int Dh) {
-    return ((R + kSplitTall.rows() - 1) / kSplitTall.rows()) * ((Dh + kSplitTall.hn() - 1) / kSplitTall.hn());
-}
-int gemm_split_tiles_n(int Dh) { return (Dh + kSplitTall.hn() - 1) / kSplitTall.hn(); }
-int gemm_split_lds_bytes(int Dh, bool full) { return (int)split_lds(kSplitTall, Dh, full); }
-
-int gemm_split_occupancy(bool full, size_t lds_bytes) {
-    int n = 0;
-    const hipError_t e = full ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_split_list_kernel<true>, kSplitTall.threads(), lds_bytes)
-                              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_split_list_kernel<false>, kSplitTall.threads(), lds_bytes);
-    return e == hipSuccess && n > 0 ? n : 1;
-}
-
-hipError_t launch_gemm_split_list(bool full, const GemmListArgs* a, int grid, size_t lds, hipStream_t stream) {
-    const dim3 g((unsigned)grid), b(kSplitTall.threads());
-    return full ? launch_kernel(gemm_split_list_kernel<true>, g, b, lds, stream, a)
-                : launch_kernel(gemm_split_list_kernel<false>, g, b, lds, stream, a);
-}
-
-hipError_t launch_gemm_split(const GemmJob& job, hipStream_t stream) {
-    if (!job.split || !gemm_split_fits(job.Dh, job.full != 0)) return hipErrorInvalidValue;
-    const int64_t cus = current_device_cus();
-    auto blocks = [&](const SplitShape& sh) {
-        return (int64_t)((job.R + sh.rows() - 1) / sh.rows()) * ((job.Dh + sh.hn() - 1) / sh.hn());
-    };
-    // tall tiles where they give half the CUs work, unless a short detector leaves most of
-    // their 192 bins a parity empty (100 bins, 34000 rows: 21 us tall, 15 us small)
-    auto width = [&](const SplitShape& sh) { return (job.Dh + sh.hn() - 1) / sh.hn() * sh.hn(); };
-    if (2 * blocks(kSplitTall) >= cus && width(kSplitTall) <= 2 * width(kSplitSmall)) return launch_split<kSplitTall.mb, kSplitTall.j, kSplitTall.wc>(job, stream);
-    if (4 * blocks(kSplitSmall) >= cus) return launch_split<kSplitSmall.mb, kSplitSmall.j, kSplitSmall.wc>(job, stream);
-    return launch_split<kSplitTiny.mb, kSplitTiny.j, kSplitTiny.wc>(job, stream);
 }
 
 hipError_t launch_gemm_grid(int prec, const GemmJob& job, hipStream_t stream) {

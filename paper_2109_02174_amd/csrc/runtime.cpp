@@ -171,7 +171,6 @@ struct Plan {
     double* d_cs = nullptr;
     float* d_cs32 = nullptr;
     void* d_taps[3] = {nullptr, nullptr, nullptr};
-    void* d_split = nullptr;         // FP32 taps as bf16 triples (detectors the split kernels take)
     float out_scale[3] = {1.0f, 1.0f, 1.0f};
     float diag[3] = {0.0f, 0.0f, 0.0f};
     int filter = 0, weighting = 0;   // fbp_filter_kind, fbp_weighting
@@ -1002,42 +1001,6 @@ int ensure_taps(Plan* p, int prec) {
         (void)hipFree(dev);
         return hip_fail(e, "hipMemcpy (filter taps)");
     }
-    // Not Shepp-Logan: its centre tap is three times its neighbours and is summed among them
-    // in one accumulator, so its images came out less exact than by the FP32 products
-    // (relative error against 64 bits over 11 geometries of 200 to 790 bins: 2.8e-7..9.5e-7
-    // by FP32 products, 1.04-1.6x that by the split; Ram-Lak, whose centre tap is added last,
-    // and Hann 0.4-1.16x, 0.8x in the mean).
-    if (prec == kFP32 && p->filter != FBP_FILTER_SHEPP_LOGAN && gemm_split_fits(p->Dh, full)) {
-        // each tap as a sum of three bf16 numbers, in eight copies shifted by one element
-        const int off = gemm_split_off(p->Dh), zlen = gemm_split_len(p->Dh);
-        const int tables = full ? 2 : 1;
-        std::vector<uint16_t> t((size_t)tables * 24 * zlen, 0);
-        for (int e = 0; e < tables; ++e)
-            for (int y = -off; y < zlen + 7 - off; ++y) {
-                const int d = e ? -2 * y : -2 * y - 1;
-                if (d < -(D - 1) || d > D - 1) continue;
-                double rest = filter_tap(p->filter, d, p->dt);
-                for (int q = 0; q < 3; ++q) {
-                    const uint16_t b = bf16_bits_rne((float)rest);
-                    const uint32_t u = (uint32_t)b << 16;
-                    float v;
-                    std::memcpy(&v, &u, 4);
-                    rest -= (double)v;
-                    for (int c = 0; c < 8; ++c) {
-                        const int z = y + off - c;
-                        if (z >= 0 && z < zlen) t[((size_t)(e * 3 + q) * 8 + c) * zlen + z] = b;
-                    }
-                }
-            }
-        e = hipMalloc(&p->d_split, t.size() * 2);
-        if (e == hipSuccess) e = hipMemcpy(p->d_split, t.data(), t.size() * 2, hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            if (p->d_split) (void)hipFree(p->d_split);
-            p->d_split = nullptr;
-            (void)hipFree(dev);
-            return hip_fail(e, "filter taps", FBP_ENOMEM);
-        }
-    }
     p->out_scale[prec] = out_scale;
     p->diag[prec] = diag;
     p->d_taps[prec] = dev;
@@ -1046,16 +1009,7 @@ int ensure_taps(Plan* p, int prec) {
 
 // ------------------------------------------------------------------ launch helpers
 
-// Geometries whose FP32 rows go through the split kernels: those with this many angles and
-// bins (60 bins 1.4x the time, 100 to 183 bins 0.85-1.14x, from 255 on 0.69-0.97x).
-// With fewer, a single slice's rows are a handful of tiles, each a serial walk over the
-// detector that the split's larger tap tables and longer MFMA chains lengthen (62 to 400
-// angles: reconstruction of one slice 1.0-1.15x the time, from 512 angles on 0.98-1.0x, 64
-// slices 0.93x).  By the geometry alone, so that a slice gets the same bits in any call.
-constexpr int kSplitAngles = 512, kSplitBins = 192;
-bool split_rows(const Plan& p) { return p.K >= kSplitAngles && p.D >= kSplitBins; }
-
-GemmJob gemm_job(const Plan& p, int prec, const float* sino, float* filt, int rows, bool split) {
+GemmJob gemm_job(const Plan& p, int prec, const float* sino, float* filt, int rows) {
     GemmJob j{};
     j.p = sino;
     j.q = filt;
@@ -1072,11 +1026,6 @@ GemmJob gemm_job(const Plan& p, int prec, const float* sino, float* filt, int ro
                          : nullptr;
     j.tiles_n = (p.D + kGemmBN - 1) / kGemmBN;
     j.groups = 1;
-    if (split && prec == kFP32 && p.d_split) {
-        j.split = p.d_split;
-        j.split_len = gemm_split_len(p.Dh);
-        j.split_off = gemm_split_off(p.Dh);
-    }
     return j;
 }
 
@@ -1133,9 +1082,8 @@ hipError_t launch_filter_rows(const Plan& p, int prec, const float* in, float* o
         j.colw = colw;
         return launch_fft_filter(j, s);
     }
-    GemmJob j = gemm_job(p, prec, in, out, rows, split_rows(p));
+    GemmJob j = gemm_job(p, prec, in, out, rows);
     j.colw = colw;
-    if (j.split) return launch_gemm_split(j, s);
     if (prec == kFP32) {
         // Tile width (the same arithmetic per output bin at every width, so the same
         // bits): 32-bin tiles when even those leave each CU at most one tile (very
@@ -1296,15 +1244,14 @@ int run_backproject(Plan& p, const ShapeParams& one, const ShapeParams& stack, i
 
 // Header at the start of a batch workspace.  The list kernels read their
 // arguments from here, so one captured graph per workspace serves every batch.
-// gemm[0] lists the Ram-Lak jobs, gemm[1] the jobs whose kernel has even taps, gemm[2]
-// and gemm[3] the same for jobs of the split kernels;
+// gemm[0] lists the Ram-Lak jobs, gemm[1] the jobs whose kernel has even taps;
 // bp[c] lists single slices of tile shape c, bpm[c] groups of slices that share
 // a geometry (stack kernel of shape c).
 struct BatchHeader {
-    GemmListArgs gemm[4];
+    GemmListArgs gemm[2];
     BpListArgs bp[kNumTileConfigs];
     BpListArgs bpm[kNumTileConfigs];
-    int32_t counts[4 + 2 * kNumTileConfigs];
+    int32_t counts[2 + 2 * kNumTileConfigs];
 };
 
 struct BatchLayout {
@@ -1321,7 +1268,7 @@ BatchLayout batch_layout(const fbp_job* jobs, int32_t n) {
     L.gemm_jobs = o;
     o = round_up(o + sizeof(GemmJob) * (size_t)n, 256);
     L.gemm_prefix = o;
-    o = round_up(o + sizeof(int32_t) * (size_t)(n + 4), 256);
+    o = round_up(o + sizeof(int32_t) * (size_t)(n + 2), 256);
     L.bp_jobs = o;
     o = round_up(o + sizeof(BpJob) * (size_t)n, 256);
     L.bp_index = o;
@@ -1389,13 +1336,13 @@ struct GraphKey {
     uintptr_t ws;
     uint32_t cfg_mask;     // tile shapes with single-slice entries
     uint32_t multi_mask;   // tile shapes with slice groups
-    int gemm_kinds;        // bit k: gemm[k] of the header has jobs
-    int gemm_lds, split_lds;
+    int gemm_kinds;        // bit 0: Ram-Lak filter jobs, bit 1: jobs with even taps
+    int gemm_lds;
     int bp_lds;
     int bpm_lds;
     bool operator<(const GraphKey& o) const {
-        return std::tie(device, prec, ws, cfg_mask, multi_mask, gemm_kinds, gemm_lds, split_lds, bp_lds, bpm_lds) <
-               std::tie(o.device, o.prec, o.ws, o.cfg_mask, o.multi_mask, o.gemm_kinds, o.gemm_lds, o.split_lds, o.bp_lds,
+        return std::tie(device, prec, ws, cfg_mask, multi_mask, gemm_kinds, gemm_lds, bp_lds, bpm_lds) <
+               std::tie(o.device, o.prec, o.ws, o.cfg_mask, o.multi_mask, o.gemm_kinds, o.gemm_lds, o.bp_lds,
                         o.bpm_lds);
     }
 };
@@ -1451,16 +1398,10 @@ void release_staging(Staging* st, bool recorded) {
 hipError_t enqueue_batch_kernels(const GraphKey& key, int cus, hipStream_t s) {
     const BatchHeader* hdr = reinterpret_cast<const BatchHeader*>(key.ws);
     hipError_t e = hipSuccess;
-    for (int kind = 0; kind < 4; ++kind) {
+    for (int kind = 0; kind < 2; ++kind) {
         if (!(key.gemm_kinds & (1 << kind))) continue;
-        const bool full = (kind & 1) != 0;
-        if (kind >= 2) {
-            const int occ = gemm_split_occupancy(full, (size_t)key.split_lds);
-            e = launch_gemm_split_list(full, &hdr->gemm[kind], cus * occ, (size_t)key.split_lds, s);
-        } else {
-            const int g_occ = gemm_occupancy(key.prec, full, (size_t)key.gemm_lds);
-            e = launch_gemm_list(key.prec, full, &hdr->gemm[kind], cus * g_occ, (size_t)key.gemm_lds, s);
-        }
+        const int g_occ = gemm_occupancy(key.prec, kind == 1, (size_t)key.gemm_lds);
+        e = launch_gemm_list(key.prec, kind == 1, &hdr->gemm[kind], cus * g_occ, (size_t)key.gemm_lds, s);
         if (e != hipSuccess) return e;
     }
     for (int c = 0; c < kNumTileConfigs; ++c) {
@@ -1554,29 +1495,22 @@ int reconstruct_batch_parallel(const fbp_job* jobs, int32_t n, const BatchLayout
     std::vector<float*> qptr((size_t)n);
     for (int32_t i = 0; i < n; ++i) {
         qptr[(size_t)i] = reinterpret_cast<float*>(wsc + L.q_off[(size_t)i]);
+        max_dh = std::max(max_dh, plans[(size_t)i]->Dh);
     }
-    // filter jobs: the Ram-Lak ones first, then those with even taps, then the same of the
-    // split kernels, each list with its own tile prefix
-    int gemm_kinds = 0, max_split_lds = 0;
-    int32_t n_gemm[4] = {0, 0, 0, 0};
+    // filter jobs: the Ram-Lak ones first, then those with even taps, each list with
+    // its own tile prefix
+    int gemm_kinds = 0;
+    int32_t n_gemm[2] = {0, 0};
     {
         int pos_g = 0, pre_g = 0;
-        for (int kind = 0; kind < 4; ++kind) {
+        for (int kind = 0; kind < 2; ++kind) {
             int64_t tiles = 0;
             gp[pre_g] = 0;
             for (int32_t i = 0; i < n; ++i) {
                 const Plan& p = *plans[(size_t)i];
-                const bool full = p.filter != FBP_FILTER_RAMLAK, split = prec == kFP32 && p.d_split && split_rows(p);
-                if (full != ((kind & 1) != 0) || split != (kind >= 2)) continue;
-                gj[pos_g] = gemm_job(p, prec, jobs[i].sino, qptr[(size_t)i], p.K, split);
-                if (split) {
-                    gj[pos_g].tiles_n = gemm_split_tiles_n(p.Dh);
-                    tiles += gemm_split_tiles(p.K, p.Dh);
-                    max_split_lds = std::max(max_split_lds, gemm_split_lds_bytes(p.Dh, full));
-                } else {
-                    tiles += (int64_t)((p.K + kGemmBM - 1) / kGemmBM) * gj[pos_g].tiles_n;
-                    max_dh = std::max(max_dh, p.Dh);
-                }
+                if ((p.filter != FBP_FILTER_RAMLAK) != (kind == 1)) continue;
+                gj[pos_g] = gemm_job(p, prec, jobs[i].sino, qptr[(size_t)i], p.K);
+                tiles += (int64_t)((p.K + kGemmBM - 1) / kGemmBM) * gj[pos_g].tiles_n;
                 if (tiles > INT32_MAX) return FBP_EUNSUPPORTED;
                 ++pos_g;
                 gp[pre_g + ++n_gemm[kind]] = (int32_t)tiles;
@@ -1599,7 +1533,7 @@ int reconstruct_batch_parallel(const fbp_job* jobs, int32_t n, const BatchLayout
         std::vector<int32_t> jobs;
         const ShapeParams* sh;
     };
-    int pos = 0, idx_off = 0, pre_off = 0, cnt_off = 4;
+    int pos = 0, idx_off = 0, pre_off = 0, cnt_off = 2;
     auto add_list = [&](BpListArgs& a, const std::vector<Item>& items, bool multi) -> int {
         int64_t tiles = 0;
         bpre[pre_off] = 0;
@@ -1683,8 +1617,7 @@ int reconstruct_batch_parallel(const fbp_job* jobs, int32_t n, const BatchLayout
     key.cfg_mask = mask;
     key.multi_mask = mmask;
     key.gemm_kinds = gemm_kinds;
-    key.gemm_lds = (gemm_kinds & 3) ? (int)round_up((size_t)gemm_lds_bytes(prec, max_dh, (gemm_kinds & 2) != 0), 8192) : 0;
-    key.split_lds = (gemm_kinds & 12) ? (int)round_up((size_t)max_split_lds, 8192) : 0;
+    key.gemm_lds = (int)round_up((size_t)gemm_lds_bytes(prec, max_dh, (gemm_kinds & 2) != 0), 8192);
     key.bp_lds = (int)round_up((size_t)max_bp_lds, 4096);
     key.bpm_lds = (int)round_up((size_t)max_bpm_lds, 4096);
     return launch_batch(key, cu_count(device), s);
@@ -2113,9 +2046,9 @@ int run_cone_filter(ConePlan& c, const float* proj, float* filt, hipStream_t s) 
         hipError_t e = launch_preweight(proj + off, rs.ptr, c.d_pw, m, (int)per_view, s);
         if (e == hipSuccess) {
             queued = true;
-            GemmJob j = gemm_job(*c.taps, kFP32, rs.ptr, filt + off, (int)(m * c.Dv), true);
+            GemmJob j = gemm_job(*c.taps, kFP32, rs.ptr, filt + off, (int)(m * c.Dv));
             j.out_scale *= 0.5f;                                       // half the kernel
-            e = j.split ? launch_gemm_split(j, s) : launch_gemm_grid(kFP32, j, s);
+            e = launch_gemm_grid(kFP32, j, s);
         }
         if (e != hipSuccess) {
             const int rc = hip_status(e, "cone-beam filter launch");
