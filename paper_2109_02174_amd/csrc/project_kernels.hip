@@ -28,6 +28,7 @@ constexpr int kProjThreads = 256;
 constexpr int kTrTile = 64;
 constexpr int kAnchorLines = 256;                   // FP64 re-anchoring period (power of 2)
 constexpr double kTwo32 = 4294967296.0;
+constexpr float kPhase = 0x1p-32f;                  // of a 32-bit phase
 constexpr int kRawWord3 = 0x00020000;               // buffer resource word 3: 32-bit data, raw (stride 0)
 constexpr int kOffImage = 0x7FFFFFF0;               // byte offset past every image: reads as 0
 
@@ -49,8 +50,10 @@ constexpr int kOffImage = 0x7FFFFFF0;               // byte offset past every im
 //    {I_0, I_1, I_2, I_3} (at most kCells a row: the host checks the group's bound), the
 //    next chunk's pixels loading while the current one is summed (double-buffered, one
 //    barrier per chunk).  A lane of a wave takes every fourth row (16 bins by 4 rows).
-//  * Positions are FP32, local to the staged window and anchored in FP64 per chunk.
-//    Weights are scaled by r = 1/a, which leaves three taps at 1 <= r <= 1.5 as 1 - f,
+//  * Positions are 6.26 fixed point, local to the angle's window and anchored in FP64 per
+//    chunk, so that a phase carries the 24 bits of its FP32 conversion wherever in the
+//    window it lies (an FP32 position of up to 64 pixels would leave it 18: on pixel noise
+//    4 to 6 times the error against 64 bits).  Weights are scaled by r = 1/a, which leaves three taps at 1 <= r <= 1.5 as 1 - f,
 //    r - |f - (2 - r)| and max(0, f + 2r - 3) of the phase f; the sum is scaled by a.
 //  * Every bin has 16 sums: rows = i + 4 q (mod 16) for lane row i and step q.  They
 //    are added in that order through LDS, whichever waves made them, so the number of
@@ -69,6 +72,9 @@ constexpr int kBins = kProjBins;                    // bins per workgroup and an
 constexpr int kLines = kProjLines;                  // image rows per chunk
 constexpr int kCells = kProjCells;                  // staged pixels per row
 constexpr int kSteps = 4;                           // rows of a chunk a lane takes: kLines / (64 / kBins)
+constexpr int kPosBits = 26;                        // fraction bits of a window-local position (six for the pixel)
+constexpr double kPosOne = 1 << kPosBits;
+static_assert(kCells <= 1 << (32 - kPosBits), "a window's positions fit");
 static_assert(kBins * (kLines / kSteps) == 64 && kLines == 2 * kStWaves && kCells == 64, "staged projector layout");
 
 template <int M>
@@ -191,9 +197,9 @@ __global__ __launch_bounds__(kStThreads) void project_staged_kernel(ProjStagedJo
     float tap[T];                                   // 1 + m - r
 #pragma unroll
     for (int m = 0; m < T; ++m) tap[m] = (float)((double)(m + 1) - inv_a);
-    float step[NS];                                 // X from row li of a chunk to the lane's row of step q
+    uint32_t step[NS];                              // X from row li of a chunk to the lane's row of step q
 #pragma unroll
-    for (int q = 0; q < NS; ++q) step[q] = (float)((double)(4 * (part + P * q)) * dl);
+    for (int q = 0; q < NS; ++q) step[q] = (uint32_t)(int)rint((double)(4 * (part + P * q)) * dl * kPosOne);
     // smallest X of the angle's bins on a chunk's rows, from the chunk's first row on row 0
     const double x_min = ((double)j0 - cd + e->b * half) * inv_a + half - inv_a + fmin(0.0, (double)(kLines - 1) * dl);
 
@@ -225,22 +231,21 @@ __global__ __launch_bounds__(kStThreads) void project_staged_kernel(ProjStagedJo
         // positions local to the angle's own window (not the group's, so that the grouping
         // does not round them differently)
         const double own = floor(fma((double)(c * kLines), dl, x_min)) - 1.0;
-        const float xr = (float)(fma((double)(c * kLines + li), dl, xj) - own);
+        const uint32_t xr = (uint32_t)((fma((double)(c * kLines + li), dl, xj) - own) * kPosOne);
         const C* __restrict__ row0 = &win[buf][li + 4 * part][0] + ((int)own - wlo);
 #pragma unroll
         for (int q = 0; q < NS; ++q) {
-            const float x = xr + step[q];           // >= 1 up to rounding: truncation is floor
-            const int i = (int)x;
-            const float f = __builtin_amdgcn_fractf(x);
-            const C* __restrict__ px = row0 + 4 * P * q * kCells + i;
+            const uint32_t x = xr + step[q];        // 1 <= x < 64 up to rounding
+            const C* __restrict__ px = row0 + 4 * P * q * kCells + (x >> kPosBits);
+            const float f = (float)(x << (32 - kPosBits));      // phase * 2^32
             float w[T];
             if constexpr (FAST3) {
-                w[0] = 1.0f - f;
-                w[1] = r - fabsf(f - r2);
-                w[2] = fmaxf(f + r3, 0.0f);
+                w[0] = fmaf(f, -kPhase, 1.0f);
+                w[1] = r - fabsf(fmaf(f, kPhase, -r2));
+                w[2] = fmaxf(fmaf(f, kPhase, r3), 0.0f);
             } else {
 #pragma unroll
-                for (int m = 0; m < T; ++m) w[m] = fmaxf(r - fabsf(f - tap[m]), 0.0f);
+                for (int m = 0; m < T; ++m) w[m] = fmaxf(r - fabsf(fmaf(f, kPhase, -tap[m])), 0.0f);
             }
 #pragma unroll
             for (int m = 0; m < T; ++m) {
