@@ -319,8 +319,8 @@ __global__ __launch_bounds__(kStThreads) void project_staged_kernel(ProjStagedJo
 //    columns whatever the fan's opening: windows stay narrow and pixels few per row.
 //  * On a row the pixels with a nonzero weight lie exactly between the crossings of the
 //    neighbouring rays, u = j - 1 and u = j + 1.  Every crossing is affine in the row, so
-//    the first tap follows ray j - 1 in FP32 steps anchored in FP64 per chunk, and the
-//    tap count is a number of the chunk (workgroup-uniform), from 1 to kFanTaps.
+//    the first tap follows ray j - 1 in fixed-point steps (7.25, for the reason given above)
+//    anchored in FP64 per chunk, and the tap count is a number of the chunk (workgroup-uniform), from 1 to kFanTaps.
 //  * With d the tap's distance from ray j along the row, l the ray's depth L/R there:
 //    L/R at the tap is l + d L'/R and u - j = d E'/R / (L/R); one reciprocal per tap
 //    serves the hat and the (R/L)^2 weight, for M S pixels.
@@ -337,6 +337,9 @@ constexpr int kFanTaps = 6;                         // most taps per row (wider 
 constexpr int kFanLines = 8;                        // image rows per chunk
 constexpr int kFanCells = 96;                       // staged pixels per row
 constexpr int kFanBorder = kFanCells;               // zeros on both sides of a row of the turned images
+constexpr int kFanPosBits = 25;                     // fraction bits of a window-local position (seven for the pixel)
+constexpr double kFanPosOne = 1 << kFanPosBits;
+static_assert(kFanCells <= 1 << (32 - kFanPosBits), "a window's positions fit");
 constexpr double kFanMinDepth = 16.0;               // depths are kept above this (the image lies beyond it)
 
 struct FanRay {                                     // crossing of ray u = cd - g with row l: p0 + l dp (pixels)
@@ -483,9 +486,9 @@ __global__ __launch_bounds__(A == 8 ? 512 : 128 * A, A >= 4 ? 4 : 1) void fan_st
     const float dep0 = (float)(1.0 - ((ray.p0 - half) * cb - half * sb) * inv_R), ddep = (float)(-(ray.dp * cb + sb) * inv_R);
     const float lq = (float)(-cb * inv_R), eq = (float)((-R * sb * inv_ds - g * cb) * inv_R);
     const float min_dep = (float)(kFanMinDepth * inv_R);
-    float step[NS];                                 // first-tap position from row li of a chunk to the row of step q
+    uint32_t step[NS];                              // first-tap position from row li of a chunk to the row of step q
 #pragma unroll
-    for (int q = 0; q < NS; ++q) step[q] = (float)((double)(4 * (part + P * q)) * below.dp);
+    for (int q = 0; q < NS; ++q) step[q] = (uint32_t)(int)rint((double)(4 * (part + P * q)) * below.dp * kFanPosOne);
 
     const int pitch = fan_pitch(N);
     const size_t plane = (size_t)fan_rows(N) * pitch;      // pixels
@@ -545,16 +548,15 @@ __global__ __launch_bounds__(A == 8 ? 512 : 128 * A, A >= 4 ? 4 : 1) void fan_st
         constexpr int T = decltype(taps)::value;
         const int own = own_lds[(active ? ia : 0) * nch + c];
         const int l0 = c * kFanLines + li;
-        const float xr = (float)(fma((double)l0, below.dp, below.p0) - (double)own);
+        const uint32_t xr = (uint32_t)((fma((double)l0, below.dp, below.p0) - (double)own) * kFanPosOne);
         const C* __restrict__ row0 = &win[buf][0][li + 4 * part][0] + (own - wlo);
 #pragma unroll
         for (int q = 0; q < NS; ++q) {
-            const float x = xr + step[q];           // >= 1 up to rounding: truncation is floor
-            const int i = (int)x;
-            const float f = __builtin_amdgcn_fractf(x);
-            const C* __restrict__ at = row0 + 4 * P * q * kFanCells + i;
+            const uint32_t x = xr + step[q];        // 1 <= x < kFanCells up to rounding
+            const C* __restrict__ at = row0 + 4 * P * q * kFanCells + (x >> kFanPosBits);
+            const float f = (float)(x << (32 - kFanPosBits));         // phase * 2^32
             const float fl = (float)(l0 + 4 * (part + P * q));
-            const float d0 = (1.0f - f) - fmaf(fl, dgap, gap0);       // first tap - ray j
+            const float d0 = fmaf(f, -kPhase, 1.0f) - fmaf(fl, dgap, gap0);       // first tap - ray j
             const float dep = fmaxf(fmaf(fl, ddep, dep0), min_dep);
 #pragma unroll
             for (int m = 0; m < T; ++m) {

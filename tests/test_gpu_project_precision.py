@@ -1,11 +1,12 @@
-"""GPU: the forward projector's error against 64 bits on an image of pixel noise.
+"""GPU: the forward projectors' error against 64 bits on an image of pixel noise.
 
 Noise has no smoothness for a position error to hide in: moving every hat by e changes a
 bin by about e times the root sum of squares of the pixel differences it meets.  Positions
 are held to about 2^-26 of a pixel, so what remains is the rounding of each weight (once or
-twice, 2^-24) and of the sums; a NumPy replay of the kernel's arithmetic gives 1.1 to 1.3
-times 2^-24 sqrt(3 N) of the noise, root mean square over the bins.  FP32 positions over a
-window of 64 pixels would give 4.4 to 7.3.  The bound is twice the replay's largest.
+twice, 2^-24) and of the sums; a NumPy replay of the kernels' arithmetic gives 1.1 to 1.3
+(parallel beam) and 1.7 to 1.9 (fan beam) times 2^-24 sqrt(3 N) of the noise, root mean
+square over the bins.  FP32 positions over a window of 64 or 96 pixels would give 4.4 to 7.3
+and 4.8 to 5.4.  The bounds are twice the replay's largest.
 """
 import math
 
@@ -38,3 +39,15 @@ def test_parallel_projector(K, kind):
     for k in (1, K // 16, K // 5, K // 3, (2 * K) // 3, K - 7):
         ref = oracle.forward_splat(x[0].astype(np.float64), 1, D, 1.0, ang[k:k + 1])[0] / K
         assert np.sqrt(np.mean((got[k] - ref) ** 2)) <= 2.6 * unit, k
+
+
+@pytest.mark.parametrize("K", [720, 721])
+def test_fan_projector(K):
+    D, R = 801, 1024.0
+    b = np.arange(K) * (2.0 * math.pi / K)
+    x = _image(1)
+    got = fbp.fbp_project(fbp.Geometry(K, D, N, 1.0, b, source_distance=R), torch.tensor(x, device="cuda")).cpu().numpy()[0]
+    unit = (2.0 * math.pi / K) * 2.0 ** -24 * math.sqrt(3.0 * N)
+    for k in (1, K // 16, K // 5, K // 3, (2 * K) // 3, K - 7):
+        ref = oracle.fan_splat(x[0].astype(np.float64), 1, D, 1.0, R, b[k:k + 1])[0] / K
+        assert np.sqrt(np.mean((got[k] - ref) ** 2)) <= 3.8 * unit, k

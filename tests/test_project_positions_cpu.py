@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 from paper_2109_02174_amd import phantom as ph
+import test_fan_staged_cpu as fan
 from test_project_windows_cpu import BINS, CELLS, LINES, base_table, group_angles, ranges
 
 ONE = 1 << 26
@@ -38,3 +39,34 @@ def test_parallel_positions(K, D, N, dt, kind):
                 phase = ((x & (ONE - 1)) << 6).astype(np.float32).astype(np.float64) * 2.0 ** -32
                 exact = xj + (l0 + l) * dl - own
                 assert np.max(np.abs((x >> 26) + phase - exact)) <= 2.0 ** -24
+
+
+@pytest.mark.parametrize("K,D,N,ds,R", [(720, 801, 512, 1.0, 1024.0), (721, 801, 512, 1.0, 1024.0), (96, 150, 90, 0.8, 130.0),
+                                        (61, 9000, 4096, 1.0, 9000.0)])
+def test_fan_positions(K, D, N, ds, R):
+    one = 1 << 25
+    b = np.arange(K) * (2.0 * math.pi / K)
+    _, tab = fan.table(b)
+    half, cd = 0.5 * (N - 1), 0.5 * (D - 1)
+    chunks = np.arange(0, N, fan.LINES)
+    for _, c0, s0, _, _ in tab[:: max(1, len(tab) // 23)]:
+        for j0 in {0, (D // 3) // BINS * BINS, (D - 1) // BINS * BINS}:
+            g0 = cd - j0
+            c, s = fan.turn_by(fan.turns(c0, s0, R, ds, g0 - 0.5 * (BINS - 1)), c0, s0)
+            below = [fan.ray(c, s, R, ds, half, g0 - i + 1.0) for i in range(BINS)]
+            p0, dp = (np.array([r[i] for r in below])[:, None] for i in (0, 1))
+            ends = [below[0][0] + l * below[0][1] for l in (chunks, chunks + fan.LINES - 1)]
+            ends += [below[-1][0] + l * below[-1][1] for l in (chunks, chunks + fan.LINES - 1)]
+            lo, hi = np.min(ends, axis=0), np.max(ends, axis=0)
+            meets = (lo - 2.0 <= N) & (hi + fan.TAPS + 3.0 >= 0.0) & (hi - lo + 5.5 <= fan.CELLS)
+            if not np.any(meets):
+                continue
+            own, l0 = np.floor(lo[meets]) - 1, chunks[meets]
+            for l in range(fan.LINES):
+                q, li = divmod(l, 4)
+                anchor = ((p0 + (l0 + li) * dp - own) * one).astype(np.int64)
+                x = anchor + np.rint(4 * q * dp * one).astype(np.int64)
+                assert np.all((x >= 0) & (x >> 25 < fan.CELLS))
+                phase = ((x & (one - 1)) << 7).astype(np.float32).astype(np.float64) * 2.0 ** -32
+                exact = p0 + (l0 + l) * dp - own
+                assert np.max(np.abs((x >> 25) + phase - exact)) <= 1.5 * 2.0 ** -24
