@@ -25,8 +25,9 @@
  * Ownership: the caller owns every device buffer and keeps it alive until the
  * work queued on `hip_stream` has finished.  The library owns only per-geometry
  * plan state (FP64 cos/sin tables, the tile choice, partial-sum planes for the
- * shapes that split a slice's angles), created on the first call for a geometry
- * and kept until process exit, plus tables made on first use: the filter taps
+ * shapes that split a slice's angles or a small volume's views), created on the
+ * first call for a geometry and kept until process exit, plus tables made on
+ * first use: the filter taps
  * of each operand precision (on the first filter call with that precision), the
  * FFT tables (first FBP_PREC_FP32_FFT call), the forward projector's padded
  * copies (first fbp_project call) and the cone-beam pre-weighting rows (first
@@ -50,10 +51,7 @@
  * reconstructed alone, in a stack or inside a batch gives bitwise-equal images,
  * whatever the autotuner chose.  Other geometries may run single slices, stacks
  * and batches with different tile shapes (and the autotuner picks shapes by
- * timing); those paths agree within the FP32 tolerance.  Cone-beam volumes of few
- * workgroups split their views over partial volumes that are added in a fixed
- * order; a call on a capturing stream does not split them, so its voxels agree
- * with the eager call's within the FP32 tolerance.
+ * timing); those paths agree within the FP32 tolerance.
  */
 #ifndef FBP_H
 #define FBP_H

@@ -32,6 +32,7 @@ namespace {
 
 constexpr int kConeThreads = kConeTile * kConeTile;
 constexpr int kConeCoef = 12;                           // per-view floats in LDS
+constexpr int kConeSerial = 8;                          // slices a workgroup of the serial form takes
 
 // Copies units of G consecutive detector columns (G = 4: one 16-byte load and
 // LDS store; the window origins, Du, the pitch and the view base are then
@@ -90,7 +91,13 @@ __device__ __forceinline__ void cone_stage(const ConeJob& job, const int* org, f
 // possible window fits).  Otherwise the four values come from global memory with
 // detector bounds checks.  Both read the same per-view window and share the
 // arithmetic.
-template <bool STAGED, int P>
+//
+// ZS slices of the block of kConeZB per workgroup: all of them, or (ZS < kConeZB) the form
+// for views in parts without planes for the parts' sums: the workgroup takes the parts one
+// after another and adds their sums in registers, in the order and so with the bits of the
+// planes.  There are few blocks then, so each goes to kConeZB / ZS workgroups, which stage
+// the same windows; no voxel's arithmetic depends on ZS.
+template <bool STAGED, int P, int ZS>
 __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
     extern __shared__ __align__(16) char smem[];
     const int KB = job.KB, N = job.N, K = job.K, Du = job.Du, Dv = job.Dv;
@@ -106,9 +113,12 @@ __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
     float* win = reinterpret_cast<float*>(nk_lds + 4);
     const int tiles = job.tiles_x * job.tiles_x;
     const int zblocks = (job.Nz + kConeZB - 1) / kConeZB;
-    const int view_part = blockIdx.x / (tiles * zblocks);              // views [K part / split, K (part+1) / split)
-    const int zb = blockIdx.x / tiles - view_part * zblocks;
-    const int tile = blockIdx.x % tiles;
+    constexpr bool kSerial = ZS < kConeZB;
+    constexpr int kSubs = kConeZB / ZS;
+    const int block = blockIdx.x / kSubs, zs = blockIdx.x % kSubs * ZS;
+    const int view_part = block / (tiles * zblocks);                   // views [K part / split, K (part+1) / split)
+    const int zb = block / tiles - view_part * zblocks;
+    const int tile = block % tiles;
     const int c0 = (tile % job.tiles_x) * kConeTile, r0 = (tile / job.tiles_x) * kConeTile;
     const int z0 = zb * kConeZB;
     const int zn = min(kConeZB, job.Nz - z0);
@@ -118,166 +128,183 @@ __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
     const float fdx = (float)dx, fdy = (float)dy;
     const double zlo = (double)z0 - job.half_z, zhi = zlo + (double)(zn - 1);
     const float zlo_dv = (float)(zlo / job.dv), inv_dv = (float)(1.0 / job.dv);
-    float acc[kConeZB];
+    if (zs >= zn) return;                               // the whole workgroup
+    float acc[ZS];
+    auto walk = [&](int part) {
 #pragma unroll
-    for (int q = 0; q < kConeZB; ++q) acc[q] = 0.0f;
-    const int k_end = (int)((int64_t)K * (view_part + 1) / job.split);
-    for (int k0 = (int)((int64_t)K * view_part / job.split); k0 < k_end;) {
-        const int nmax = min(KB, k_end - k0);
-        __syncthreads();                                // previous block's reads done
-        if (threadIdx.x < 64) {                         // wave 0: one view per lane (KB <= 64)
-            int size = 0;
-            if ((int)threadIdx.x < nmax) {
-                // FP64, per view: the in-plane map (as the fan beam) and the window
-                // of detector cells the tile's voxels can reach.  u = N/L and
-                // rho = R/L are linear-fractional in (x, y), so over the tile their
-                // extremes sit at the corners; v = z rho / dv + cv is then extreme
-                // at a corner of (z, rho).  One cell of margin on each side covers
-                // FP32 rounding, and the clamps below keep every read inside the
-                // window regardless.
-                const int k = k0 + threadIdx.x;
-                const double c = job.cs[2 * k], sn = job.cs[2 * k + 1];
-                const double R = job.R, du = job.du;
-                const double xt = (double)c0 - job.half_pix, yt = (double)r0 - job.half_pix;
-                const double Lt = R - (c * xt + sn * yt);
-                const double Nt = R * (-sn * xt + c * yt);
-                double Lmin = INFINITY, Lmax = -INFINITY, umin = INFINITY, umax = -INFINITY;
-                for (int q = 0; q < 4; ++q) {
-                    const double ex = (q & 1) ? (double)(cw - 1) : 0.0, ey = (q & 2) ? (double)(rh - 1) : 0.0;
-                    const double L = Lt - c * ex - sn * ey;
-                    const double u = (Nt + R * (-sn * ex + c * ey)) / (L * du);
-                    Lmin = fmin(Lmin, L);
-                    Lmax = fmax(Lmax, L);
-                    umin = fmin(umin, u);
-                    umax = fmax(umax, u);
+        for (int q = 0; q < ZS; ++q) acc[q] = 0.0f;
+        const int k_end = (int)((int64_t)K * (part + 1) / job.split);
+        for (int k0 = (int)((int64_t)K * part / job.split); k0 < k_end;) {
+            const int nmax = min(KB, k_end - k0);
+            __syncthreads();                                // previous block's reads done
+            if (threadIdx.x < 64) {                         // wave 0: one view per lane (KB <= 64)
+                int size = 0;
+                if ((int)threadIdx.x < nmax) {
+                    // FP64, per view: the in-plane map (as the fan beam) and the window
+                    // of detector cells the tile's voxels can reach.  u = N/L and
+                    // rho = R/L are linear-fractional in (x, y), so over the tile their
+                    // extremes sit at the corners; v = z rho / dv + cv is then extreme
+                    // at a corner of (z, rho).  One cell of margin on each side covers
+                    // FP32 rounding, and the clamps below keep every read inside the
+                    // window regardless.
+                    const int k = k0 + threadIdx.x;
+                    const double c = job.cs[2 * k], sn = job.cs[2 * k + 1];
+                    const double R = job.R, du = job.du;
+                    const double xt = (double)c0 - job.half_pix, yt = (double)r0 - job.half_pix;
+                    const double Lt = R - (c * xt + sn * yt);
+                    const double Nt = R * (-sn * xt + c * yt);
+                    double Lmin = INFINITY, Lmax = -INFINITY, umin = INFINITY, umax = -INFINITY;
+                    for (int q = 0; q < 4; ++q) {
+                        const double ex = (q & 1) ? (double)(cw - 1) : 0.0, ey = (q & 2) ? (double)(rh - 1) : 0.0;
+                        const double L = Lt - c * ex - sn * ey;
+                        const double u = (Nt + R * (-sn * ex + c * ey)) / (L * du);
+                        Lmin = fmin(Lmin, L);
+                        Lmax = fmax(Lmax, L);
+                        umin = fmin(umin, u);
+                        umax = fmax(umax, u);
+                    }
+                    const double rlo = R / Lmax, rhi = R / Lmin;
+                    const double vmin = fmin(fmin(zlo * rlo, zlo * rhi), fmin(zhi * rlo, zhi * rhi)) / job.dv;
+                    const double vmax = fmax(fmax(zlo * rlo, zlo * rhi), fmax(zhi * rlo, zhi * rhi)) / job.dv;
+                    // column origin rounded down to the alignment, width up to it
+                    const int i0 = (int)floor(umin + job.cu) - 1;
+                    const int i0a = i0 - (((i0 % A) + A) % A);
+                    const int j0 = (int)floor(vmin + job.cv) - 1;
+                    const int ncw = (int)floor(umax + job.cu) + 3 - i0a;
+                    const int nc = min(pitch, (ncw + A - 1) / A * A);
+                    const int nr = min(RW, (int)floor(vmax + job.cv) + 4 - j0);   // one more row: see the clamp
+                    const double G = ((double)i0a - job.cu) * du;
+                    const double a0 = Nt - G * Lt, a1 = -R * sn + G * c, a2 = R * c + G * sn;
+                    float* cf = coef + kConeCoef * threadIdx.x;
+                    cf[0] = (float)(a0 * job.inv_duR);
+                    cf[1] = (float)(a1 * job.inv_duR);
+                    cf[2] = (float)(a2 * job.inv_duR);
+                    cf[3] = (float)(job.cv - (double)j0);
+                    cf[4] = (float)(Lt * job.inv_R);
+                    cf[5] = (float)(-c * job.inv_R);
+                    cf[6] = (float)(-sn * job.inv_R);
+                    cf[7] = (float)(nc - 2);
+                    cf[8] = (float)(nr - 2);
+                    int* og = org + 8 * threadIdx.x;
+                    og[0] = i0a;
+                    og[1] = j0;
+                    og[2] = nc;
+                    og[3] = nr;
+                    size = nr * pitch;
                 }
-                const double rlo = R / Lmax, rhi = R / Lmin;
-                const double vmin = fmin(fmin(zlo * rlo, zlo * rhi), fmin(zhi * rlo, zhi * rhi)) / job.dv;
-                const double vmax = fmax(fmax(zlo * rlo, zlo * rhi), fmax(zhi * rlo, zhi * rhi)) / job.dv;
-                // column origin rounded down to the alignment, width up to it
-                const int i0 = (int)floor(umin + job.cu) - 1;
-                const int i0a = i0 - (((i0 % A) + A) % A);
-                const int j0 = (int)floor(vmin + job.cv) - 1;
-                const int ncw = (int)floor(umax + job.cu) + 3 - i0a;
-                const int nc = min(pitch, (ncw + A - 1) / A * A);
-                const int nr = min(RW, (int)floor(vmax + job.cv) + 4 - j0);   // one more row: see the clamp
-                const double G = ((double)i0a - job.cu) * du;
-                const double a0 = Nt - G * Lt, a1 = -R * sn + G * c, a2 = R * c + G * sn;
-                float* cf = coef + kConeCoef * threadIdx.x;
-                cf[0] = (float)(a0 * job.inv_duR);
-                cf[1] = (float)(a1 * job.inv_duR);
-                cf[2] = (float)(a2 * job.inv_duR);
-                cf[3] = (float)(job.cv - (double)j0);
-                cf[4] = (float)(Lt * job.inv_R);
-                cf[5] = (float)(-c * job.inv_R);
-                cf[6] = (float)(-sn * job.inv_R);
-                cf[7] = (float)(nc - 2);
-                cf[8] = (float)(nr - 2);
-                int* og = org + 8 * threadIdx.x;
-                og[0] = i0a;
-                og[1] = j0;
-                og[2] = nc;
-                og[3] = nr;
-                size = nr * pitch;
-            }
-            if constexpr (STAGED) {
-                // pack the windows: LDS offsets from a prefix sum over the lanes; the
-                // block takes the views whose windows end within cap (a prefix of them)
-                int incl = size;
+                if constexpr (STAGED) {
+                    // pack the windows: LDS offsets from a prefix sum over the lanes; the
+                    // block takes the views whose windows end within cap (a prefix of them)
+                    int incl = size;
 #pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const int y = __shfl_up(incl, d, 64);
-                    if ((int)threadIdx.x >= d) incl += y;
+                    for (int d = 1; d < 64; d <<= 1) {
+                        const int y = __shfl_up(incl, d, 64);
+                        if ((int)threadIdx.x >= d) incl += y;
+                    }
+                    if ((int)threadIdx.x < nmax) org[8 * threadIdx.x + 4] = incl - size;
+                    const unsigned long long fit = __ballot((int)threadIdx.x < nmax && incl <= job.cap);
+                    if (threadIdx.x == 0) nk_lds[0] = __popcll(fit);
                 }
-                if ((int)threadIdx.x < nmax) org[8 * threadIdx.x + 4] = incl - size;
-                const unsigned long long fit = __ballot((int)threadIdx.x < nmax && incl <= job.cap);
-                if (threadIdx.x == 0) nk_lds[0] = __popcll(fit);
-            }
-        }
-        __syncthreads();
-        int nk = nmax;
-        if constexpr (STAGED) {
-            nk = nk_lds[0];
-            for (int kq = 0; kq < nk; kq += 4) {
-                if (job.vec4)
-                    cone_stage<4>(job, org, win, kq, nk, k0, pitch);
-                else
-                    cone_stage<1>(job, org, win, kq, nk, k0, pitch);
             }
             __syncthreads();
-        }
-        if (inside) {
-            for (int kk = 0; kk < nk; ++kk) {
-                const float4 nf = *reinterpret_cast<const float4*>(coef + kConeCoef * kk);
-                const float4 df = *reinterpret_cast<const float4*>(coef + kConeCoef * kk + 4);
-                const float vmax = coef[kConeCoef * kk + 8];
-                const float den = fmaf(df.z, fdy, fmaf(df.y, fdx, df.x));
-                const float num = fmaf(nf.z, fdy, fmaf(nf.y, fdx, nf.x));
-                const float rho = __builtin_amdgcn_rcpf(den);          // R / L
-                const float u = __builtin_amdgcn_fmed3f(num * rho, 0.0f, df.w);
-                const float w = rho * rho;
-                const int iu = (int)u;
-                const float fu = u - (float)iu;
-                const float wb = w * fu, wa = w - wb;                  // column weights
-                const float a = rho * inv_dv;                          // rows per slice
-                const float v0 = fmaf(zlo_dv, rho, nf.w);              // window row of the block's first slice
-                if constexpr (STAGED) {
-                    // byte offset of the sample's window column in LDS, kept in one
-                    // register so each sample's address is one 24-bit multiply-add
-                    unsigned boff = (unsigned)((const char*)(win + org[8 * kk + 4] + iu) - smem);
-                    asm volatile("" : "+v"(boff));
-                    auto sample = [&](int q, float v) {
-                        const int iv = (int)v;
-                        const float fv = __builtin_amdgcn_fractf(v);   // v >= 0: v - floor(v)
-                        const float* __restrict__ p =
-                            reinterpret_cast<const float*>(smem + __umul24((unsigned)iv, (unsigned)(4 * pitch)) + boff);
-                        const float c0v = fmaf(fv, p[pitch] - p[0], p[0]);
-                        const float c1v = fmaf(fv, p[pitch + 1] - p[1], p[1]);
-                        acc[q] = fmaf(wb, c1v, fmaf(wa, c0v, acc[q]));
-                    };
-                    // v is monotone in q (a > 0, and FP32 rounding keeps the order), so
-                    // when the first and last slices' rows lie in the window every
-                    // slice's does and the clamp can be left out
-                    if (v0 >= 0.0f && fmaf((float)(kConeZB - 1), a, v0) <= vmax) {
+            int nk = nmax;
+            if constexpr (STAGED) {
+                nk = nk_lds[0];
+                for (int kq = 0; kq < nk; kq += 4) {
+                    if (job.vec4)
+                        cone_stage<4>(job, org, win, kq, nk, k0, pitch);
+                    else
+                        cone_stage<1>(job, org, win, kq, nk, k0, pitch);
+                }
+                __syncthreads();
+            }
+            if (inside) {
+                for (int kk = 0; kk < nk; ++kk) {
+                    const float4 nf = *reinterpret_cast<const float4*>(coef + kConeCoef * kk);
+                    const float4 df = *reinterpret_cast<const float4*>(coef + kConeCoef * kk + 4);
+                    const float vmax = coef[kConeCoef * kk + 8];
+                    const float den = fmaf(df.z, fdy, fmaf(df.y, fdx, df.x));
+                    const float num = fmaf(nf.z, fdy, fmaf(nf.y, fdx, nf.x));
+                    const float rho = __builtin_amdgcn_rcpf(den);          // R / L
+                    const float u = __builtin_amdgcn_fmed3f(num * rho, 0.0f, df.w);
+                    const float w = rho * rho;
+                    const int iu = (int)u;
+                    const float fu = u - (float)iu;
+                    const float wb = w * fu, wa = w - wb;                  // column weights
+                    const float a = rho * inv_dv;                          // rows per slice
+                    const float v0 = fmaf(zlo_dv, rho, nf.w);              // window row of the block's first slice
+                    if constexpr (STAGED) {
+                        // byte offset of the sample's window column in LDS, kept in one
+                        // register so each sample's address is one 24-bit multiply-add
+                        unsigned boff = (unsigned)((const char*)(win + org[8 * kk + 4] + iu) - smem);
+                        asm volatile("" : "+v"(boff));
+                        auto sample = [&](int q, float v) {
+                            const int iv = (int)v;
+                            const float fv = __builtin_amdgcn_fractf(v);   // v >= 0: v - floor(v)
+                            const float* __restrict__ p =
+                                reinterpret_cast<const float*>(smem + __umul24((unsigned)iv, (unsigned)(4 * pitch)) + boff);
+                            const float c0v = fmaf(fv, p[pitch] - p[0], p[0]);
+                            const float c1v = fmaf(fv, p[pitch + 1] - p[1], p[1]);
+                            acc[q] = fmaf(wb, c1v, fmaf(wa, c0v, acc[q]));
+                        };
+                        // v is monotone in q (a > 0, and FP32 rounding keeps the order), so
+                        // when the first and last slices' rows lie in the window every
+                        // slice's does and the clamp can be left out
+                        if (v0 >= 0.0f && fmaf((float)(kConeZB - 1), a, v0) <= vmax) {
 #pragma unroll
-                        for (int q = 0; q < kConeZB; ++q) sample(q, fmaf((float)q, a, v0));
+                            for (int q = 0; q < ZS; ++q) sample(q, fmaf((float)(zs + q), a, v0));
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < ZS; ++q)
+                                sample(q, __builtin_amdgcn_fmed3f(fmaf((float)(zs + q), a, v0), 0.0f, vmax));
+                        }
                     } else {
-#pragma unroll
-                        for (int q = 0; q < kConeZB; ++q)
-                            sample(q, __builtin_amdgcn_fmed3f(fmaf((float)q, a, v0), 0.0f, vmax));
-                    }
-                } else {
-                    const float* __restrict__ qv = job.q + (size_t)(k0 + kk) * Dv * Du;
-                    const int col = org[8 * kk] + iu;
-                    const int row0 = org[8 * kk + 1];
-                    auto at = [&](int cc, int rr) {
-                        return ((unsigned)cc < (unsigned)Du && (unsigned)rr < (unsigned)Dv) ? qv[rr * Du + cc] : 0.0f;
-                    };
+                        const float* __restrict__ qv = job.q + (size_t)(k0 + kk) * Dv * Du;
+                        const int col = org[8 * kk] + iu;
+                        const int row0 = org[8 * kk + 1];
+                        auto at = [&](int cc, int rr) {
+                            return ((unsigned)cc < (unsigned)Du && (unsigned)rr < (unsigned)Dv) ? qv[rr * Du + cc] : 0.0f;
+                        };
 #pragma unroll 4
-                    for (int q = 0; q < kConeZB; ++q) {
-                        const float v = __builtin_amdgcn_fmed3f(fmaf((float)q, a, v0), 0.0f, vmax);
-                        const int iv = (int)v;
-                        const float fv = __builtin_amdgcn_fractf(v);
-                        const int row = row0 + iv;
-                        const float p00 = at(col, row), p01 = at(col + 1, row);
-                        const float p10 = at(col, row + 1), p11 = at(col + 1, row + 1);
-                        const float c0v = fmaf(fv, p10 - p00, p00);
-                        const float c1v = fmaf(fv, p11 - p01, p01);
-                        acc[q] = fmaf(wb, c1v, fmaf(wa, c0v, acc[q]));
+                        for (int q = 0; q < ZS; ++q) {
+                            const float v = __builtin_amdgcn_fmed3f(fmaf((float)(zs + q), a, v0), 0.0f, vmax);
+                            const int iv = (int)v;
+                            const float fv = __builtin_amdgcn_fractf(v);
+                            const int row = row0 + iv;
+                            const float p00 = at(col, row), p01 = at(col + 1, row);
+                            const float p10 = at(col, row + 1), p11 = at(col + 1, row + 1);
+                            const float c0v = fmaf(fv, p10 - p00, p00);
+                            const float c1v = fmaf(fv, p11 - p01, p01);
+                            acc[q] = fmaf(wb, c1v, fmaf(wa, c0v, acc[q]));
+                        }
                     }
                 }
             }
+            k0 += nk;
         }
-        k0 += nk;
+    };
+    walk(kSerial ? 0 : view_part);
+    if constexpr (kSerial) {
+        float sum[ZS];
+#pragma unroll
+        for (int q = 0; q < ZS; ++q) sum[q] = acc[q];
+        for (int part = 1; part < job.split; ++part) {
+            walk(part);
+#pragma unroll
+            for (int q = 0; q < ZS; ++q) sum[q] += acc[q];
+        }
+#pragma unroll
+        for (int q = 0; q < ZS; ++q) acc[q] = sum[q];
     }
     if (inside) {
         // split views: unscaled sums into the part's plane
-        float* __restrict__ vol = job.split > 1 ? job.part + (size_t)view_part * job.Nz * N * N : job.vol;
-        const float scale = job.split > 1 ? 1.0f : job.scale;
+        const bool planes = !kSerial && job.split > 1;
+        float* __restrict__ vol = planes ? job.part + (size_t)view_part * job.Nz * N * N : job.vol;
+        const float scale = planes ? 1.0f : job.scale;
 #pragma unroll
-        for (int q = 0; q < kConeZB; ++q)
-            if (q < zn)
-                vol[((size_t)(z0 + q) * N + (r0 + dy)) * N + (c0 + dx)] = acc[q] * scale;
+        for (int q = 0; q < ZS; ++q)
+            if (zs + q < zn)
+                vol[((size_t)(z0 + zs + q) * N + (r0 + dy)) * N + (c0 + dx)] = acc[q] * scale;
     }
 }
 
@@ -300,10 +327,12 @@ __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
 // four waves a SIMD.  Measured there, filter included: 1.72 ms against 2.54 ms.  Three
 // waves a SIMD without spills: 2.14 ms; 12 slices a workgroup 2.00 ms; one end of the
 // window area for every item (two barriers an item): 1.86 ms.
+constexpr int kConeRotSerial = 4;                       // slices a workgroup of the serial form takes
 constexpr int kConeRotItems = 32;                       // items whose windows are made at once
 constexpr int kConeRotRegs = 3;                         // cells a thread prefetches (the rest, of the largest windows, load late)
 constexpr int kConeRotInts = 16;                        // per-item words in LDS
 
+template <int ZS>                                       // slices per workgroup (see cone_bp_kernel)
 __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) {
     extern __shared__ __align__(16) char smem[];
     const int N = job.N, K4 = job.K >> 2, Du = job.Du, Dv = job.Dv;
@@ -313,9 +342,12 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
     const int tiles_y = ((N >> 1) + kConeTile - 1) / kConeTile;
     const int tiles = job.tiles_x * tiles_y;
     const int zblocks = (job.Nz + kConeRotZB - 1) / kConeRotZB;
-    const int view_part = blockIdx.x / (tiles * zblocks);    // base views [K4 part / split, K4 (part+1) / split)
-    const int zb = blockIdx.x / tiles - view_part * zblocks;
-    const int tile = blockIdx.x % tiles;
+    constexpr bool kSerial = ZS < kConeRotZB;
+    constexpr int kSubs = kConeRotZB / ZS;
+    const int block = blockIdx.x / kSubs, zs = blockIdx.x % kSubs * ZS;
+    const int view_part = block / (tiles * zblocks);         // base views [K4 part / split, K4 (part+1) / split)
+    const int zb = block / tiles - view_part * zblocks;
+    const int tile = block % tiles;
     const int c0 = (tile % job.tiles_x) * kConeTile, r0 = (tile / job.tiles_x) * kConeTile;
     const int z0 = zb * kConeRotZB;
     const int zn = min(kConeRotZB, job.Nz - z0);
@@ -326,15 +358,17 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
     const float fdx = (float)dx, fdy = (float)dy;
     const double zlo = (double)z0 - job.half_z, zhi = zlo + (double)(zn - 1);
     const float zlo_dv = (float)(zlo / job.dv), inv_dv = (float)(1.0 / job.dv);
-    const int first = 4 * (int)((int64_t)K4 * view_part / job.split);
-    const int items = 4 * (int)((int64_t)K4 * (view_part + 1) / job.split);      // one past the last
+    if (zs >= zn) return;                                // the whole workgroup
+    auto part_begin = [&](int part) { return 4 * (int)((int64_t)K4 * part / job.split); };
+    int first = part_begin(kSerial ? 0 : view_part);     // items of the part in hand: its first, one past its last
+    int items = part_begin(kSerial ? 1 : view_part + 1);
     const size_t view = (size_t)Dv * Du;
 
-    float acc[4][kConeRotZB];
+    float acc[4][ZS];
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int q = 0; q < kConeRotZB; ++q) acc[m][q] = 0.0f;
+        for (int q = 0; q < ZS; ++q) acc[m][q] = 0.0f;
 
     // windows of the items i0 .. i0 + kConeRotItems - 1 (see cone_bp_kernel), one per lane of wave 0
     auto windows = [&](int i0) {
@@ -478,7 +512,7 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
         // clamped into the window whatever the rounding (leaving the clamp out where the first
         // and last slices' rows lie inside measured no faster)
 #pragma unroll
-        for (int q = 0; q < kConeRotZB; ++q) sample(q, __builtin_amdgcn_fmed3f(fmaf((float)q, a, v0), 0.0f, vmax));
+        for (int q = 0; q < ZS; ++q) sample(q, __builtin_amdgcn_fmed3f(fmaf((float)(zs + q), a, v0), 0.0f, vmax));
     };
     const bool inside = dx < cw && dy < rh;
     // The items' windows lie at the two ends of the window area in turn, so that one barrier
@@ -496,48 +530,70 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
         if (inside) compute(turn, it, pitch, dst);
         last = size;
     };
-    for (int i0 = first; i0 < items; i0 += kConeRotItems) {
-        __syncthreads();
-        windows(i0);
-        __syncthreads();
-        load(i0);
-        const int end = min(items, i0 + kConeRotItems);
-        for (int it = i0; it < end; it += 4) {
-            step(std::integral_constant<int, 0>{}, it);
-            step(std::integral_constant<int, 1>{}, it + 1);
-            step(std::integral_constant<int, 2>{}, it + 2);
-            step(std::integral_constant<int, 3>{}, it + 3);
+    auto walk = [&]() {
+        for (int i0 = first; i0 < items; i0 += kConeRotItems) {
+            __syncthreads();
+            windows(i0);
+            __syncthreads();
+            load(i0);
+            const int end = min(items, i0 + kConeRotItems);
+            for (int it = i0; it < end; it += 4) {
+                step(std::integral_constant<int, 0>{}, it);
+                step(std::integral_constant<int, 1>{}, it + 1);
+                step(std::integral_constant<int, 2>{}, it + 2);
+                step(std::integral_constant<int, 3>{}, it + 3);
+            }
         }
+    };
+    walk();
+    if constexpr (kSerial) {
+        float sum[4][ZS];
+        auto each = [&](auto f) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int q = 0; q < ZS; ++q) f(sum[m][q], acc[m][q]);
+        };
+        each([](float& s, float& a) { s = a; a = 0.0f; });
+        for (int part = 1; part < job.split; ++part) {
+            first = items;
+            items = part_begin(part + 1);
+            walk();
+            each([](float& s, float& a) { s += a; a = 0.0f; });
+        }
+        each([](float& s, float& a) { a = s; });
     }
 
     // turns 0 and 2 lie along rows; 1 and 3 along columns, transposed through LDS so that
     // consecutive lanes write consecutive addresses
     const size_t plane = (size_t)N * N;
-    float* __restrict__ vol = job.split > 1 ? job.part + (size_t)view_part * job.Nz * plane : job.vol;
-    const float scale = job.split > 1 ? 1.0f : job.scale;      // split views: unscaled sums into the part's plane
+    const bool planes = !kSerial && job.split > 1;
+    float* __restrict__ vol = (planes ? job.part + (size_t)view_part * job.Nz * plane : job.vol) + (z0 + zs) * plane;
+    const float scale = planes ? 1.0f : job.scale;             // split views: unscaled sums into the part's plane
+    const int zq = zn - zs;                                    // slices of the workgroup that exist
     if (inside) {
         const int r = r0 + dy, c = c0 + dx;
 #pragma unroll
-        for (int q = 0; q < kConeRotZB; ++q)
-            if (q < zn) {
-                vol[(z0 + q) * plane + (size_t)r * N + c] = acc[0][q] * scale;
-                vol[(z0 + q) * plane + (size_t)(N - 1 - r) * N + (N - 1 - c)] = acc[2][q] * scale;
+        for (int q = 0; q < ZS; ++q)
+            if (q < zq) {
+                vol[q * plane + (size_t)r * N + c] = acc[0][q] * scale;
+                vol[q * plane + (size_t)(N - 1 - r) * N + (N - 1 - c)] = acc[2][q] * scale;
             }
     }
-    float* tr = reinterpret_cast<float*>(win);               // [kConeRotZB][16][17]
+    float* tr = reinterpret_cast<float*>(win);               // [ZS][16][17]
 #pragma unroll
     for (int m = 1; m < 4; m += 2) {
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < kConeRotZB; ++q) tr[(q * kConeTile + dx) * (kConeTile + 1) + dy] = acc[m][q];
+        for (int q = 0; q < ZS; ++q) tr[(q * kConeTile + dx) * (kConeTile + 1) + dy] = acc[m][q];
         __syncthreads();
         // lane (dx, dy) now holds column c0 + dy, row r0 + dx of the tile
         if (dy < cw && dx < rh) {
             const int r = r0 + dx, c = c0 + dy;
             const size_t o = m == 1 ? (size_t)c * N + (N - 1 - r) : (size_t)(N - 1 - c) * N + r;
 #pragma unroll
-            for (int q = 0; q < kConeRotZB; ++q)
-                if (q < zn) vol[(z0 + q) * plane + o] = tr[(q * kConeTile + dy) * (kConeTile + 1) + dx] * scale;
+            for (int q = 0; q < ZS; ++q)
+                if (q < zq) vol[q * plane + o] = tr[(q * kConeTile + dy) * (kConeTile + 1) + dx] * scale;
         }
     }
 }
@@ -573,10 +629,10 @@ template <int I>
 hipError_t launch_pitch(int pitch, const ConeJob& job, dim3 grid, size_t lds, hipStream_t stream) {
     if constexpr (I < (int)(sizeof(kConePitches) / sizeof(int))) {
         if (pitch == kConePitches[I])
-            return launch_kernel(cone_bp_kernel<true, kConePitches[I]>, grid, dim3(kConeThreads), lds, stream, job);
+            return launch_kernel(cone_bp_kernel<true, kConePitches[I], kConeZB>, grid, dim3(kConeThreads), lds, stream, job);
         return launch_pitch<I + 1>(pitch, job, grid, lds, stream);
     } else {
-        return launch_kernel(cone_bp_kernel<true, 0>, grid, dim3(kConeThreads), lds, stream, job);
+        return launch_kernel(cone_bp_kernel<true, 0, kConeZB>, grid, dim3(kConeThreads), lds, stream, job);
     }
 }
 
@@ -610,10 +666,12 @@ hipError_t launch_cone_rot(ConeJob job, hipStream_t stream) {
     const size_t lds = cone_rot_lds_bytes(job.cap);
     if ((int64_t)job.Dv * job.Du * 4 > 0x7FFFFFF0) return hipErrorInvalidValue;     // a view's buffer range
     const int64_t tiles = (int64_t)job.tiles_x * (((job.N >> 1) + kConeTile - 1) / kConeTile);
-    if (job.split < 1 || job.split > job.K / 4 || (job.split > 1 && !job.part)) return hipErrorInvalidValue;
-    const int64_t blocks = tiles * ((job.Nz + kConeRotZB - 1) / kConeRotZB) * job.split;
+    if (job.split < 1 || job.split > job.K / 4) return hipErrorInvalidValue;
+    const bool serial = job.split > 1 && !job.part;
+    const int64_t blocks = tiles * ((job.Nz + kConeRotZB - 1) / kConeRotZB) * (serial ? kConeRotZB / kConeRotSerial : job.split);
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    return launch_kernel(cone_rot_kernel, dim3((unsigned)blocks), dim3(kConeThreads), lds, stream, job);
+    return launch_kernel(serial ? cone_rot_kernel<kConeRotSerial> : cone_rot_kernel<kConeRotZB>, dim3((unsigned)blocks),
+                         dim3(kConeThreads), lds, stream, job);
 }
 
 hipError_t launch_cone_centre(const ConeJob& job, hipStream_t stream) {
@@ -630,12 +688,17 @@ hipError_t launch_cone_bp(const ConeJob& job, bool staged, hipStream_t stream) {
     if (staged && (int64_t)(job.WV + 1) * job.pitch > job.cap) return hipErrorInvalidValue;   // one window must fit
     const size_t lds = cone_lds_bytes(job.KB, job.cap, staged);
     if (lds > kConeLdsBudget) return hipErrorInvalidValue;
-    if (job.split < 1 || job.split > job.K || (job.split > 1 && !job.part)) return hipErrorInvalidValue;
-    const int64_t blocks = (int64_t)job.tiles_x * job.tiles_x * ((job.Nz + kConeZB - 1) / kConeZB) * job.split;
+    if (job.split < 1 || job.split > job.K) return hipErrorInvalidValue;
+    const bool serial = job.split > 1 && !job.part;
+    const int64_t blocks = (int64_t)job.tiles_x * job.tiles_x * ((job.Nz + kConeZB - 1) / kConeZB) *
+                           (serial ? kConeZB / kConeSerial : job.split);
     if (blocks > INT32_MAX) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks);
+    const dim3 grid((unsigned)blocks), block(kConeThreads);
+    if (serial)
+        return launch_kernel(staged ? cone_bp_kernel<true, 0, kConeSerial> : cone_bp_kernel<false, 0, kConeSerial>, grid, block,
+                             lds, stream, job);
     return staged ? launch_pitch<0>(job.pitch, job, grid, lds, stream)
-                  : launch_kernel(cone_bp_kernel<false, 0>, grid, dim3(kConeThreads), lds, stream, job);
+                  : launch_kernel(cone_bp_kernel<false, 0, kConeZB>, grid, block, lds, stream, job);
 }
 
 }  // namespace fbp

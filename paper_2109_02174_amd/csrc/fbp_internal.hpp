@@ -346,7 +346,8 @@ struct ConeJob {
                            // pitch >= WL + 7 for the wider aligned windows)
     int32_t tiles_x;       // ceil(N / kConeTile)
     int32_t split;         // parts the views are split over (1: none)
-    float* part;           // split > 1: [split][Nz][N][N] unscaled partial sums
+    float* part;           // split > 1: [split][Nz][N][N] unscaled partial sums, or null: the parts one
+                           // after another, added in registers (the same bits)
     float scale;           // 2 pi / K
 };
 constexpr int kConeTile = 16;

@@ -1881,7 +1881,7 @@ struct ConePlan {
     bool staged = true;
     bool rot = false;                // quarter-turn form
     int rot_WV = 0;                  // its row bound
-    PartBuffer part;                 // small volumes: partial sums of the view parts (planes = parts)
+    PartBuffer part;                 // partial sums of the view parts (planes: the parts, 1 unless the volume is small)
     double half_span = 0.0;
     RowScratch rows;
 };
@@ -1934,6 +1934,7 @@ int make_cone_plan(ConePlan* c) {
     const int zb = c->rot ? kConeRotZB : kConeZB;
     const int64_t blocks = (int64_t)tx * ty * ((c->Nz + zb - 1) / zb), cus = cu_count(c->device);
     const size_t vol = sizeof(float) * (size_t)c->Nz * (size_t)c->N * (size_t)c->N;
+    c->part.planes = 1;
     if (blocks <= 2 * cus) {
         const int64_t most = std::min<int64_t>({kMaxSplit, c->K / 8, (int64_t)(kConePartBytes / vol)});
         c->part.planes = (int)std::max<int64_t>(1, std::min<int64_t>(most, (4 * cus + blocks - 1) / blocks));
@@ -2093,27 +2094,29 @@ int run_cone_backproject(ConePlan& c, const float* filt, float* vol, hipStream_t
         j.WV = c.rot_WV;
         j.tiles_x = ((c.N + 1) / 2 + kConeTile - 1) / kConeTile;
     }
+    auto launch = [&] { return c.rot ? launch_cone_rot(j, s) : launch_cone_bp(j, c.staged, s); };
+    j.split = c.part.planes;
+    hipError_t e = hipSuccess;
     // The partial sums are used by one call at a time, in stream order; a stream that is
-    // being captured cannot wait for another call's event, so captured calls do not split
-    j.split = 1;
+    // being captured cannot wait for another call's event, so captured calls (and plans
+    // that found no memory for the sums) run the parts one after another
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool split = c.part.ptr && hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
-    std::unique_lock<std::mutex> lock(c.part.mu, std::defer_lock);
-    if (split) {
-        lock.lock();
+    if (j.split > 1 && c.part.ptr && hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone) {
+        std::lock_guard<std::mutex> lock(c.part.mu);
         if (c.part.recorded) FBP_TRY_HIP(hipStreamWaitEvent(s, c.part.free_ev, 0));
-        j.split = c.part.planes;
         j.part = c.part.ptr;
-    }
-    hipError_t e = c.rot ? launch_cone_rot(j, s) : launch_cone_bp(j, c.staged, s);
-    if (e == hipSuccess && split) {
-        e = launch_combine_parts(j.part, vol, 1, j.split, (size_t)c.Nz * c.N * c.N, j.scale, s);
-        if (e != hipSuccess) {
-            const int rc = hip_status(e, "partial-sum kernel launch");
-            return fail_after_queued(rc, c.part.free_ev, &c.part.recorded, s);
+        e = launch();
+        if (e == hipSuccess) {
+            e = launch_combine_parts(j.part, vol, 1, j.split, (size_t)c.Nz * c.N * c.N, j.scale, s);
+            if (e != hipSuccess) {
+                const int rc = hip_status(e, "partial-sum kernel launch");
+                return fail_after_queued(rc, c.part.free_ev, &c.part.recorded, s);
+            }
+            FBP_TRY_HIP(hipEventRecord(c.part.free_ev, s));
+            c.part.recorded = true;
         }
-        FBP_TRY_HIP(hipEventRecord(c.part.free_ev, s));
-        c.part.recorded = true;
+    } else {
+        e = launch();
     }
     if (e == hipSuccess && c.rot && (c.N & 1)) e = launch_cone_centre(j, s);
     return e == hipErrorInvalidValue ? FBP_EUNSUPPORTED : hip_status(e, "cone-beam backprojection launch");
