@@ -461,6 +461,16 @@ int hip_fail(hipError_t e, const char* what, int status = FBP_EHIP) {
         if (fbp_e_ != hipSuccess) return hip_fail(fbp_e_, #call);           \
     } while (0)
 
+// Device memory that a call can do without: null where there is none, with no error left
+// behind for the caller's next check (an earlier one of the caller's stays).
+void* spare_memory(size_t bytes) {
+    const bool clean = hipPeekAtLastError() == hipSuccess;
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    if (clean) (void)hipGetLastError();
+    return nullptr;
+}
+
 // Compute units of a device (cached).
 int cu_count(int device) {
     static std::mutex mu;
@@ -1957,13 +1967,11 @@ int make_cone_plan(ConePlan* c) {
     if (e == hipSuccess) e = hipMemcpy(c->d_cs, cs.data(), sizeof(double) * cs.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->d_pw, pw.data(), sizeof(float) * pw.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->rows.free_ev, hipEventDisableTiming);
-    if (e == hipSuccess && c->part.planes > 1) {
-        e = hipMalloc(&c->part.ptr, vol * (size_t)c->part.planes);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&c->part.free_ev, hipEventDisableTiming);
+    if (e == hipSuccess && c->part.planes > 1) {         // without them: one part after another
+        e = hipEventCreateWithFlags(&c->part.free_ev, hipEventDisableTiming);
+        if (e == hipSuccess) c->part.ptr = static_cast<float*>(spare_memory(vol * (size_t)c->part.planes));
     }
     if (e != hipSuccess) {
-        if (c->part.ptr) (void)hipFree(c->part.ptr);
-        c->part.ptr = nullptr;
         if (c->d_cs) (void)hipFree(c->d_cs);
         if (c->d_pw) (void)hipFree(c->d_pw);
         c->d_cs = nullptr;
