@@ -965,7 +965,6 @@ ProjLayout project_layout(const double* cs, int K, int N) {
     ProjLayout L;
     L.fast3 = r_min >= 1.0 && r_max <= 1.5;
     L.T = L.fast3 ? 3 : (int)fmin(ceil(2.0 * r_max), 1e9);
-    L.slice_floats = (size_t)N * (size_t)N;         // the transposed copy (staged projector)
     const double pad = ceil(65.0 * r_max) + L.T + 4.0;
     const double pitch = (double)N + 2.0 * pad;
     if (!(pitch < 1e9)) {
@@ -974,6 +973,7 @@ ProjLayout project_layout(const double* cs, int K, int N) {
     }
     L.pad = (int)pad;
     L.pitch = (int)pitch;
+    L.slice_floats = (size_t)2 * (size_t)(N + 1) * (size_t)L.pitch;
     return L;
 }
 

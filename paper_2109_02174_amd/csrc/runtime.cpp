@@ -674,9 +674,9 @@ ProjLayout parallel_project_layout(const Plan& p, std::vector<ProjAngle>* tab) {
     if (L.A > 0) {
         L.M = quarter ? 4 : 2;
         L.n0 = n0;
+        L.slice_floats = (size_t)p.N * (size_t)p.N;     // the transposed copy
     } else {
         tab->clear();
-        L.slice_floats = (size_t)2 * (size_t)(p.N + 1) * (size_t)L.pitch;
     }
     return L;
 }
@@ -716,6 +716,50 @@ ProjLayout fan_projector_layout(const Plan& p, std::vector<ProjAngle>* tab) {
         tab->clear();
     }
     return L;
+}
+
+// Layout and buffers of a plan's projector.  The staged fan-beam form wants two to four times the
+// memory of the one-lane kernel's copies: where that is short it takes fewer slices at a
+// time (the same bits), and where one slice does not fit, the one-lane kernel's copies.
+int make_proj_scratch(const Plan& p, ProjScratch* ps) {
+    const bool fan = p.R > 0.0;
+    std::vector<ProjAngle> tab;
+    ProjLayout L = fan ? fan_projector_layout(p, &tab) : parallel_project_layout(p, &tab);
+    if (L.T == 0) return FBP_EUNSUPPORTED;
+    auto most = [&] {
+        return (int)std::max<size_t>(1, std::min<size_t>(16, ((size_t)256 << 20) / (sizeof(float) * L.slice_floats)));
+    };
+    auto bytes = [&](int slices) { return sizeof(float) * L.slice_floats * (size_t)slices; };
+    int slices = most();
+    hipError_t e = hipSuccess;
+    if (L.A > 0) {
+        ps->d_tab = static_cast<ProjAngle*>(spare_memory(sizeof(ProjAngle) * tab.size()));
+        for (; ps->d_tab && slices > 0; slices /= 2)
+            if ((ps->ptr = static_cast<float*>(spare_memory(bytes(slices))))) break;
+        if (ps->ptr) {
+            e = hipMemcpy(ps->d_tab, tab.data(), sizeof(ProjAngle) * tab.size(), hipMemcpyHostToDevice);
+            ps->n_base = (int)tab.size();
+        } else {
+            if (ps->d_tab) (void)hipFree(ps->d_tab);
+            ps->d_tab = nullptr;
+            L = fan ? fan_project_layout(p) : project_layout(p.cs.data(), p.K, p.N);
+        }
+    }
+    if (!ps->ptr) {
+        slices = most();
+        e = hipMalloc(&ps->ptr, bytes(slices));
+    }
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ps->free_ev, hipEventDisableTiming);
+    if (e != hipSuccess) {
+        if (ps->d_tab) (void)hipFree(ps->d_tab);
+        if (ps->ptr) (void)hipFree(ps->ptr);
+        ps->d_tab = nullptr;
+        ps->ptr = nullptr;
+        return hip_fail(e, "hipMalloc (projector copies)", FBP_ENOMEM);
+    }
+    ps->layout = L;
+    ps->slices = slices;
+    return FBP_OK;
 }
 
 bool plan_matches(const Plan& p, const fbp_geom* g) {
@@ -2283,27 +2327,8 @@ int fbp_project(const fbp_geom* geom, int32_t n_slices, const float* d_image, fl
     ProjScratch& ps = p->proj;
     std::lock_guard<std::mutex> lock(ps.mu);
     if (!ps.ptr) {
-        std::vector<ProjAngle> tab;
-        ps.layout = fan ? fan_projector_layout(*p, &tab) : parallel_project_layout(*p, &tab);
-        if (ps.layout.T == 0) return FBP_EUNSUPPORTED;
-        const size_t slice_bytes = sizeof(float) * ps.layout.slice_floats;
-        const int slices = (int)std::max<size_t>(1, std::min<size_t>(16, ((size_t)256 << 20) / slice_bytes));
-        hipError_t e = hipMalloc(&ps.ptr, slice_bytes * (size_t)slices);
-        if (e == hipSuccess && !tab.empty()) {
-            e = hipMalloc(&ps.d_tab, sizeof(ProjAngle) * tab.size());
-            if (e == hipSuccess)
-                e = hipMemcpy(ps.d_tab, tab.data(), sizeof(ProjAngle) * tab.size(), hipMemcpyHostToDevice);
-            ps.n_base = (int)tab.size();
-        }
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&ps.free_ev, hipEventDisableTiming);
-        if (e != hipSuccess) {
-            if (ps.d_tab) (void)hipFree(ps.d_tab);
-            if (ps.ptr) (void)hipFree(ps.ptr);
-            ps.d_tab = nullptr;
-            ps.ptr = nullptr;
-            return hip_fail(e, "hipMalloc (projector copies)", FBP_ENOMEM);
-        }
-        ps.slices = slices;
+        rc = make_proj_scratch(*p, &ps);
+        if (rc != FBP_OK) return rc;
     }
     const hipStream_t s = (hipStream_t)hip_stream;
     const ProjLayout& L = ps.layout;
