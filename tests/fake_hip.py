@@ -49,8 +49,10 @@ def run(body):
     with tempfile.TemporaryDirectory() as tmp:
         so = os.path.join(tmp, "libfakehip.so")
         subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"), "-o", so], check=True)
-        done = subprocess.run([sys.executable, "-c", _CHILD + body + "\nprint('RESULT ' + json.dumps(result))", so, ROOT],
-                              capture_output=True, text=True, timeout=300)
+        script = os.path.join(tmp, "child.py")
+        with open(script, "w") as f:
+            f.write(_CHILD + body + "\nprint('RESULT ' + json.dumps(result))\n")
+        done = subprocess.run([sys.executable, script, so, ROOT], capture_output=True, text=True, timeout=300)
     lines = [l for l in done.stdout.splitlines() if l.startswith("RESULT ")]
     assert done.returncode == 0 and lines, done.stdout + done.stderr
     return json.loads(lines[-1][7:])

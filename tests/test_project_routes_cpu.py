@@ -1,0 +1,25 @@
+"""Which projector kernel a geometry takes, on a HIP runtime of host memory (fake_hip.cpp)."""
+import json
+
+from fake_hip import run
+from test_gpu_project_taps import CASES, angles
+
+
+def test_every_case_takes_the_kernel_it_names():
+    plain = [[K, D, N, dt, list(angles(K, kind)), weighting] for K, D, N, dt, kind, weighting, *_ in CASES]
+    got = run(f"""
+result = []
+for K, D, N, dt, ang, weighting in json.loads({json.dumps(json.dumps(plain))}):
+    g = fbp.Geometry(K, D, N, dt, np.array(ang), weighting=weighting)
+    fake.fake_reset()
+    assert call("fbp_project", g, 1, A, C) == 0
+    result.append(launched()[-1])
+""")
+    for case, (kernel, values, blocks) in zip(CASES, got):
+        assert kernel == case[6] and values[:len(case[7])] == case[7], (case, kernel, values)
+
+
+def test_every_staged_form_is_among_the_cases():
+    """M = 4 with one to four taps, M = 2 with one to three, each three-tap form twice."""
+    forms = {tuple(c[7]) for c in CASES if c[6] == "project_staged_kernel"}
+    assert forms == {(4, 1, 0), (4, 2, 0), (4, 3, 0), (4, 3, 1), (4, 4, 0), (2, 1, 0), (2, 2, 0), (2, 3, 0), (2, 3, 1)}
