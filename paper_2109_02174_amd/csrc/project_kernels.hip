@@ -87,21 +87,15 @@ template <>
 struct Cell<2> {
     using type = float2;
 };
-template <>
-struct Cell<1> {
-    using type = float;
-};
 __device__ __forceinline__ void unpack(const float4& c, float (&v)[4]) { v[0] = c.x; v[1] = c.y; v[2] = c.z; v[3] = c.w; }
 __device__ __forceinline__ void unpack(const float2& c, float (&v)[2]) { v[0] = c.x; v[1] = c.y; }
-__device__ __forceinline__ void unpack(const float& c, float (&v)[1]) { v[0] = c; }
 __device__ __forceinline__ void pack(const float (&v)[4], float4& c) { c = make_float4(v[0], v[1], v[2], v[3]); }
 __device__ __forceinline__ void pack(const float (&v)[2], float2& c) { c = make_float2(v[0], v[1]); }
-__device__ __forceinline__ void pack(const float (&v)[1], float& c) { c = v[0]; }
 
 // Loads of one chunk by one lane: pixel `px` of two rows of the M turned images, as
 //     I_0[l][p] = img[l][p]            I_1[l][p] = tr[N-1-l][p]
 //     I_2[l][p] = img[N-1-l][N-1-p]    I_3[l][p] = tr[l][N-1-p]
-// (tr the transposed image).  M = 4: all four; M = 2: I_s, I_{s+2}; M = 1: I_s alone.
+// (tr the transposed image).  M = 4: all four; M = 2: I_s, I_{s+2}.
 // Rows and pixels off the image read as 0 (range-checked buffer loads).
 template <int M>
 struct TurnRows {
@@ -124,11 +118,9 @@ struct TurnRows {
             v[1] = at(tr, lb, fwd);
             v[2] = at(img, lb, rev);
             v[3] = at(tr, la, rev);
-        } else if constexpr (M == 2) {
+        } else {
             v[0] = s ? at(tr, lb, fwd) : at(img, la, fwd);
             v[1] = s ? at(tr, la, rev) : at(img, lb, rev);
-        } else {
-            v[0] = s == 0 ? at(img, la, fwd) : s == 1 ? at(tr, lb, fwd) : s == 2 ? at(img, lb, rev) : at(tr, la, rev);
         }
     }
 };
@@ -1025,8 +1017,10 @@ hipError_t launch_staged_taps(const ProjStagedJob& job, int A, int T, bool fast3
         case 1: return launch_staged_parts<M, 1, false>(job, A, grid, lds, stream);
         case 2: return launch_staged_parts<M, 2, false>(job, A, grid, lds, stream);
         case 3: return launch_staged_parts<M, 3, false>(job, A, grid, lds, stream);
-        default: return launch_staged_parts<M, 4, false>(job, A, grid, lds, stream);
+        default: break;
     }
+    if constexpr (M == 4) return launch_staged_parts<4, 4, false>(job, A, grid, lds, stream);
+    return hipErrorInvalidValue;                        // four taps only in quarter-turn lists
 }
 
 hipError_t launch_project_staged(ProjStagedJob job, int M, int A_max, int T, bool fast3, int n_slices,
