@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256) void preweight_kernel(const float* __restrict_
 // M slices per workgroup (a stack of one geometry): the map of a pixel and view
 // (rho, u, window index) is made once and applied to the M slices' windows, so a
 // slice's arithmetic and summation order are those of M = 1 (bitwise equal).
-template <int M>
+template <int M, bool SHORT = false>
 __global__ __launch_bounds__(kFanThreads) void fan_bp_kernel(FanJob job) {
     extern __shared__ __align__(16) char smem[];
     const int KB = job.KB, WL = job.WL, N = job.N, K = job.K, D = job.D;
@@ -63,10 +63,10 @@ __global__ __launch_bounds__(kFanThreads) void fan_bp_kernel(FanJob job) {
     const int kpart = (K + job.split - 1) / job.split;
     const int kbeg = job.split > 1 ? g * kpart : 0;
     const int kend = job.split > 1 ? min(K, kbeg + kpart) : K;
-    // slices g M .. g M + M - 1; a group past the end of the stack reads its last slice again
-    // and does not write it
+    // slices g M .. g M + M - 1; SHORT: a group past the end of the stack reads its last slice
+    // again and does not write it
     const float* __restrict__ qs = job.q + (job.split > 1 ? (size_t)0 : (size_t)g * M * qstride);
-    const int last = M == 1 ? 0 : min(M, job.n_slices - g * M) - 1;    // the group's last slice of the stack
+    const int last = SHORT ? min(M, job.n_slices - g * M) - 1 : M - 1; // the group's last slice of the stack
     const float inv_wl = 1.0f / (float)WL;
     float acc[M];
 #pragma unroll
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kFanThreads) void fan_bp_kernel(FanJob job) {
 // coordinate (D-1)/2 on every view (weight 1); the workgroup of the first tile
 // sums it from the filtered rows after its tile (lanes over views, then a fixed
 // butterfly).
-template <int M>
+template <int M, bool SHORT = false>
 __global__ __launch_bounds__(kFanThreads) void fan_rot_kernel(FanJob job) {
     extern __shared__ __align__(16) char smem[];
     const int KB = job.KB, WL = job.WL, N = job.N, K = job.K, D = job.D;
@@ -228,10 +228,10 @@ __global__ __launch_bounds__(kFanThreads) void fan_rot_kernel(FanJob job) {
     const int kpart = (K4 + job.split - 1) / job.split;
     const int kbeg = job.split > 1 ? g * kpart : 0;
     const int kend = job.split > 1 ? min(K4, kbeg + kpart) : K4;
-    // slices g M .. g M + M - 1; a group past the end of the stack reads its last slice again
-    // and does not write it
+    // slices g M .. g M + M - 1; SHORT: a group past the end of the stack reads its last slice
+    // again and does not write it
     const float* __restrict__ qs = job.q + (job.split > 1 ? (size_t)0 : (size_t)g * M * qstride);
-    const int last = M == 1 ? 0 : min(M, job.n_slices - g * M) - 1;    // the group's last slice of the stack
+    const int last = SHORT ? min(M, job.n_slices - g * M) - 1 : M - 1; // the group's last slice of the stack
     const float inv_wl = 1.0f / (float)WL;
     float acc[4][M];
 #pragma unroll
@@ -404,12 +404,12 @@ size_t fan_rot_lds_bytes(int KB, int WL, int M) {
 }
 
 // Quarter-turn form (N >= 2, K = 4 K4 with the views in quarter turns, K D 4 bytes
-// addressable by a buffer resource): groups of M slices (the last one may be short);
-// a single slice may split its base views over job.split parts.
+// addressable by a buffer resource): groups of M slices (the last group of two may be
+// short); a single slice may split its base views over job.split parts.
 hipError_t launch_fan_rot(const FanJob& job, int n_slices, int M, int KBm, hipStream_t stream) {
     if (n_slices <= 0) return hipSuccess;
     if (job.N < 2 || (job.K & 3) || job.K < 4 || job.KB < 1 || 4 * job.KB > kFanThreads || job.WL < 2 ||
-        (M != 1 && M != 2 && M != 4) || (M > 1 && (KBm < 1 || 4 * KBm > kFanThreads)) ||
+        (M != 1 && M != 2 && M != 4) || (M == 4 && n_slices % 4) || (M > 1 && (KBm < 1 || 4 * KBm > kFanThreads)) ||
         !fan_rot_addressable(job.K, job.D, job.WL) || job.tiles_x != ((job.N + 1) / 2 + kFanTile - 1) / kFanTile)
         return hipErrorInvalidValue;
     const int64_t tiles = (int64_t)job.tiles_x * ((job.N / 2 + kFanTile - 1) / kFanTile);
@@ -421,8 +421,8 @@ hipError_t launch_fan_rot(const FanJob& job, int n_slices, int M, int KBm, hipSt
         const size_t lds = fan_rot_lds_bytes(KBm, job.WL, M);
         const int64_t blocks = tiles * ((n_slices + M - 1) / M);
         if (blocks > INT32_MAX || lds > kFanLdsBudget) return hipErrorInvalidValue;
-        return (M == 2) ? launch_kernel(fan_rot_kernel<2>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j)
-                        : launch_kernel(fan_rot_kernel<4>, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j);
+        auto* kernel = M == 4 ? fan_rot_kernel<4> : n_slices % 2 ? fan_rot_kernel<2, true> : fan_rot_kernel<2>;
+        return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j);
     }
     const size_t lds = fan_rot_lds_bytes(job.KB, job.WL, 1);
     if (lds > kFanLdsBudget) return hipErrorInvalidValue;
@@ -439,11 +439,12 @@ hipError_t launch_preweight(const float* in, float* out, const float* w, int64_t
     return launch_kernel(preweight_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, in, out, w, n, D);
 }
 
-// n_slices of one geometry: groups of M through the M-slice kernel (KBm views per block
-// for it; the last group may be short); a single slice may split its views over parts.
+// n_slices of one geometry: groups of M through the M-slice kernel (KBm views per block for
+// it; the last group of two may be short); a single slice may split its views over parts.
 hipError_t launch_fan_bp(const FanJob& job, int n_slices, int M, int KBm, hipStream_t stream) {
     if (n_slices <= 0) return hipSuccess;
-    if (job.KB < 1 || job.WL < 2 || (M != 1 && M != 2 && M != 4) || (M > 1 && KBm < 1)) return hipErrorInvalidValue;
+    if (job.KB < 1 || job.WL < 2 || (M != 1 && M != 2 && M != 4) || (M > 1 && KBm < 1) || (M == 4 && n_slices % 4))
+        return hipErrorInvalidValue;
     const int64_t tiles = (int64_t)job.tiles_x * job.tiles_x;
     FanJob j = job;
     j.n_slices = n_slices;
@@ -455,10 +456,8 @@ hipError_t launch_fan_bp(const FanJob& job, int n_slices, int M, int KBm, hipStr
     const size_t lds = fan_lds_bytes(j.KB, j.WL, M);
     const int64_t blocks = tiles * (j.split > 1 ? j.split : (n_slices + M - 1) / M);
     if (blocks > INT32_MAX || lds > kFanLdsBudget) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks), block(kFanThreads);
-    return M == 1   ? launch_kernel(fan_bp_kernel<1>, grid, block, lds, stream, j)
-           : M == 2 ? launch_kernel(fan_bp_kernel<2>, grid, block, lds, stream, j)
-                    : launch_kernel(fan_bp_kernel<4>, grid, block, lds, stream, j);
+    auto* kernel = M == 1 ? fan_bp_kernel<1> : M == 4 ? fan_bp_kernel<4> : n_slices % 2 ? fan_bp_kernel<2, true> : fan_bp_kernel<2>;
+    return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kFanThreads), lds, stream, j);
 }
 
 }  // namespace fbp

@@ -310,7 +310,7 @@ struct FanJob {
 constexpr int kFanTile = 16;
 constexpr size_t kFanLdsBudget = 48 * 1024;
 size_t fan_lds_bytes(int KB, int WL, int M);
-// n_slices in groups of M (1, 2 or 4; KBm views per block of a group).
+// n_slices in groups of M (1, 2, or 4 where they divide n_slices; KBm views per block of a group).
 hipError_t launch_fan_bp(const FanJob& job, int n_slices, int M, int KBm, hipStream_t stream);
 // Quarter-turn form (N >= 2; K = 4 K4 with view k + i K4 at angle b_k + i pi/2):
 // a workgroup owns a tile of the base region, rows [0, N/2) by columns [0, (N+1)/2)

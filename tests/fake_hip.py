@@ -36,7 +36,7 @@ def launched():
     out = []
     for i in range(fake.fake_launches()):
         m = re.search(r"([a-z_0-9]+_kernel(?:_1)?)(I[A-Za-z0-9_]*?E)?E", fake.fake_kernel(i).decode())
-        name = re.sub(r"^.*?\\d+(?=[a-z])", "", m.group(1))
+        name = re.sub(r"^.*\\d+(?=[a-z])", "", m.group(1))
         values = [int(v) for v in re.findall(r"L[ib](\\d+)E", m.group(0))]
         out.append((name, values, fake.fake_blocks(i)))
     return out
