@@ -53,8 +53,9 @@ constexpr int kOffImage = 0x7FFFFFF0;               // byte offset past every im
 //  * Positions are 6.26 fixed point, local to the angle's window and anchored in FP64 per
 //    chunk, so that a phase carries the 24 bits of its FP32 conversion wherever in the
 //    window it lies (an FP32 position of up to 64 pixels would leave it 18: on pixel noise
-//    4 to 6 times the error against 64 bits).  Weights are scaled by r = 1/a, which leaves three taps at 1 <= r <= 1.5 as 1 - f,
-//    r - |f - (2 - r)| and max(0, f + 2r - 3) of the phase f; the sum is scaled by a.
+//    4 to 6 times the error against 64 bits).  Weights are scaled by r = 1/a, which leaves
+//    three taps at 1 <= r <= 1.5 as 1 - f, r - |f - (2 - r)| and max(0, f + 2r - 3) of the
+//    phase f; the sum is scaled by a.
 //  * Every bin has 16 sums: rows = i + 4 q (mod 16) for lane row i and step q.  They
 //    are added in that order through LDS, whichever waves made them, so the number of
 //    angles per workgroup never changes a bit.  No atomics; each bin is written once.
@@ -312,7 +313,8 @@ __global__ __launch_bounds__(kStThreads) void project_staged_kernel(ProjStagedJo
 //  * On a row the pixels with a nonzero weight lie exactly between the crossings of the
 //    neighbouring rays, u = j - 1 and u = j + 1.  Every crossing is affine in the row, so
 //    the first tap follows ray j - 1 in fixed-point steps (7.25, for the reason given above)
-//    anchored in FP64 per chunk, and the tap count is a number of the chunk (workgroup-uniform), from 1 to kFanTaps.
+//    anchored in FP64 per chunk, and the tap count is a number of the chunk
+//    (workgroup-uniform), from 1 to kFanTaps.
 //  * With d the tap's distance from ray j along the row, l the ray's depth L/R there:
 //    L/R at the tap is l + d L'/R and u - j = d E'/R / (L/R); one reciprocal per tap
 //    serves the hat and the (R/L)^2 weight, for M S pixels.
@@ -1013,20 +1015,16 @@ template <int M>
 hipError_t launch_staged_taps(const ProjStagedJob& job, int A, int T, bool fast3, dim3 grid, size_t lds,
                               hipStream_t stream) {
     if (fast3) return launch_staged_parts<M, 3, true>(job, A, grid, lds, stream);
-    switch (T) {
-        case 1: return launch_staged_parts<M, 1, false>(job, A, grid, lds, stream);
-        case 2: return launch_staged_parts<M, 2, false>(job, A, grid, lds, stream);
-        case 3: return launch_staged_parts<M, 3, false>(job, A, grid, lds, stream);
-        default: break;
-    }
+    if (T == 2) return launch_staged_parts<M, 2, false>(job, A, grid, lds, stream);
+    if (T == 3) return launch_staged_parts<M, 3, false>(job, A, grid, lds, stream);
     if constexpr (M == 4) return launch_staged_parts<4, 4, false>(job, A, grid, lds, stream);
-    return hipErrorInvalidValue;                        // four taps only in quarter-turn lists
+    return hipErrorInvalidValue;                        // four taps: quarter-turn lists only
 }
 
 hipError_t launch_project_staged(ProjStagedJob job, int M, int A_max, int T, bool fast3, int n_slices,
                                  hipStream_t stream) {
     if (n_slices <= 0) return hipSuccess;
-    if (T < 1 || T > kProjMaxTaps || A_max < 1 || A_max > kProjWaves || (M != 2 && M != 4) || (fast3 && T != 3))
+    if (T < 2 || T > kProjMaxTaps || A_max < 1 || A_max > kProjWaves || (M != 2 && M != 4) || (fast3 && T != 3))
         return hipErrorInvalidValue;
     job.Dh = (job.D + 1) / 2;
     job.bin_blocks = (job.Dh + kBins - 1) / kBins;

@@ -656,10 +656,12 @@ std::vector<ProjAngle> project_base_angles(const Plan& p, bool quarter, int* n0)
 
 // Kernel and scratch layout of a parallel-beam projector: the staged one where enough
 // neighbouring base angles share a window to pay for staging it, else padded copies.
-// Measured over 110 random calls, one lane per bin against staged: quarter-turn lists with
-// four or eight angles to a window 1.1-2.1x, with two 0.9-1.1x, with one 0.6-0.8x; other
-// lists (half the bins per walk) with eight 1.0-1.5x (four taps 0.88x), with four
-// 0.9-1.06x; images below about 112^2 0.92-1.08x either way.
+// Time of one lane per bin over that of the staged form, 800 random calls of 112^2 to 1024^2
+// and 1 to 17 slices.  Quarter-turn lists, two to four taps: 0.96-3.6 with four or eight angles
+// to a window (0.9-1.1 with two, 0.6-0.8 with one).  Other lists (half the bins per walk),
+// eight angles, two taps: 0.99-2.2; three taps: 0.85-1.2 below 136^2, 1.02-2.2 from there on;
+// four taps 0.88; two to four taps with four angles 0.9-1.06.  One tap, which one lane loads and
+// weighs at once: 0.7-1.3, other lists 0.56-0.84.  Images below about 112^2: 0.92-1.08.
 ProjLayout parallel_project_layout(const Plan& p, std::vector<ProjAngle>* tab) {
     ProjLayout L = project_layout(p.cs.data(), p.K, p.N);
     if (L.T == 0) return L;
@@ -667,7 +669,8 @@ ProjLayout parallel_project_layout(const Plan& p, std::vector<ProjAngle>* tab) {
     int n0 = 0;
     *tab = project_base_angles(p, quarter, &n0);
     L.A = project_group_angles(*tab, n0, L.T, p.N);
-    if (L.A < (quarter ? 4 : 8) || (!quarter && L.T > 3) || p.N < 112) L.A = 0;
+    const bool pays = L.T >= 2 && (quarter ? L.A >= 4 && p.N >= 112 : L.A >= 8 && L.T <= 3 && p.N >= (L.T == 3 ? 136 : 112));
+    if (!pays) L.A = 0;
     if (L.A > 0) {
         L.M = quarter ? 4 : 2;
         L.n0 = n0;

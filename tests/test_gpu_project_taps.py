@@ -23,22 +23,25 @@ STAGED, LANE = "project_staged_kernel", "project_kernel"
 
 # K, D, N, dt, list, weighting, kernel, its first template values: (M, T, FAST3), or (T, FAST3) of the one-lane kernel
 CASES = [
-    (720, 189, 112, 1.0, "uniform", "uniform", STAGED, [4, 3, 1]),      # half detector of 95 bins
+    (720, 189, 112, 1.0, "uniform", "uniform", STAGED, [4, 3, 1]),      # the smallest staged image; half detector of 95 bins
     (720, 252, 131, 0.75, "uniform", "uniform", STAGED, [4, 3, 0]),     # 126
     (720, 255, 113, 0.75, "quarter", "uniform", STAGED, [4, 3, 0]),     # 128
-    (1441, 257, 128, 0.75, "uniform", "uniform", STAGED, [2, 3, 0]),    # 129
-    (1601, 256, 127, 0.8, "golden", "uniform", STAGED, [2, 3, 0]),
+    (1441, 257, 136, 0.75, "uniform", "uniform", STAGED, [2, 3, 0]),    # 129; the smallest of other lists, three taps
+    (1601, 256, 141, 0.8, "golden", "uniform", STAGED, [2, 3, 0]),
     (720, 320, 130, 0.6, "uniform", "uniform", STAGED, [4, 2, 0]),
+    (720, 513, 120, 0.4, "uniform", "uniform", STAGED, [4, 2, 0]),      # 257
     (1501, 321, 129, 0.6, "golden", "uniform", STAGED, [2, 2, 0]),
-    (720, 513, 120, 0.35, "uniform", "uniform", STAGED, [4, 1, 0]),     # 257
-    (1401, 509, 121, 0.34, "golden", "uniform", STAGED, [2, 1, 0]),     # 255
+    (1501, 321, 112, 0.6, "golden", "uniform", STAGED, [2, 2, 0]),
     (720, 460, 400, 1.25, "uniform", "uniform", STAGED, [4, 4, 0]),     # four angles to a window
-    (1601, 191, 130, 1.0, "golden", "angle-gaps", STAGED, [2, 3, 1]),
+    (1601, 191, 137, 1.0, "golden", "angle-gaps", STAGED, [2, 3, 1]),
     (1600, 191, 130, 1.0, "uniform", "angle-gaps", STAGED, [4, 3, 1]),
-    (1701, 250, 129, 0.75, "golden", "angle-gaps", STAGED, [2, 3, 0]),
-    (1601, 150, 130, 1.25, "golden", "uniform", LANE, [4, 0]),          # other lists: at most three taps
-    (720, 159, 111, 1.0, "uniform", "uniform", LANE, [3, 1]),           # below the smallest staged image
-    (64, 183, 128, 1.0, "golden", "uniform", LANE, [3, 1]),             # too few angles to a window
+    (1701, 250, 139, 0.75, "golden", "angle-gaps", STAGED, [2, 3, 0]),
+    (720, 513, 150, 0.35, "uniform", "uniform", LANE, [1, 0]),          # one tap
+    (1401, 509, 150, 0.34, "golden", "uniform", LANE, [1, 0]),          # other lists: two or three taps
+    (1601, 150, 150, 1.25, "golden", "uniform", LANE, [4, 0]),
+    (1601, 191, 135, 1.0, "golden", "uniform", LANE, [3, 1]),           # below the smallest staged images
+    (720, 159, 111, 1.0, "uniform", "uniform", LANE, [3, 1]),
+    (64, 183, 150, 1.0, "golden", "uniform", LANE, [3, 1]),             # too few angles to a window
     (100, 300, 300, 1.0, "uniform", "uniform", LANE, [3, 1]),
 ]
 

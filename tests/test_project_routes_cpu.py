@@ -20,6 +20,6 @@ for K, D, N, dt, ang, weighting in json.loads({json.dumps(json.dumps(plain))}):
 
 
 def test_every_staged_form_is_among_the_cases():
-    """M = 4 with one to four taps, M = 2 with one to three, each three-tap form twice."""
+    """M = 4 with two to four taps, M = 2 with two and three, each three-tap form twice."""
     forms = {tuple(c[7]) for c in CASES if c[6] == "project_staged_kernel"}
-    assert forms == {(4, 1, 0), (4, 2, 0), (4, 3, 0), (4, 3, 1), (4, 4, 0), (2, 1, 0), (2, 2, 0), (2, 3, 0), (2, 3, 1)}
+    assert forms == {(4, 2, 0), (4, 3, 0), (4, 3, 1), (4, 4, 0), (2, 2, 0), (2, 3, 0), (2, 3, 1)}
