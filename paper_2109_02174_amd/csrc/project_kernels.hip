@@ -1067,31 +1067,46 @@ int fan_group_views(const std::vector<ProjAngle>& tab, int N, int D, double R, d
             turn_by(q, c, s);
             for (double g : {g0 + 1.0, g0 - kProjBins}) {              // rays stay within 60 degrees of the columns
                 const double dx = g * ds * s - R * c, dy = -g * ds * c - R * s;
-                if (!(dy >= 0.5 * std::hypot(dx, dy))) return false;
+                if (!(dy >= 0.0 && 3.0 * dy * dy >= dx * dx)) return false;
             }
             ed[i] = fan_edges(c, s, R, inv_ds, half, g0);
         }
-        // 0: no pixel of the image, 1: fits, -1: does not
-        auto chunk = [&](int c) {
-            double lo = INFINITY, hi = -INFINITY, width = 0.0;
+        auto reach = [&](int c) {                   // of all the views on the rows of a chunk
+            FanReach all{INFINITY, -INFINITY, 0.0};
             for (int i = 0; i < na; ++i) {
                 const FanReach f = fan_reach(ed[i], (double)(c * kFanLines), (double)(c * kFanLines + kFanLines - 1));
-                lo = std::min(lo, f.lo);
-                hi = std::max(hi, f.hi);
-                width = std::max(width, f.width);
+                all.lo = std::min(all.lo, f.lo);
+                all.hi = std::max(all.hi, f.hi);
+                all.width = std::max(all.width, f.width);
             }
-            const double taps = std::ceil(width);
-            if (lo - 2.0 > (double)N || hi + taps + 3.0 < 0.0) return 0;
-            return width <= kFanTaps - 0.01 && hi - lo + taps + 4.5 <= (double)kFanCells ? 1 : -1;
+            return all;
         };
-        for (int c = 0; c < nch; ++c)
-            if (const int f = chunk(c)) {
-                if (f < 0) return false;
-                break;
+        auto left = [](const FanReach& f) { return f.hi + f.width + 4.0 < 0.0; };      // of every pixel of the image
+        auto right = [&](const FanReach& f) { return f.lo - 2.0 > (double)N; };
+        // the first chunk from c towards `end` that meets the image, past `end` if none does:
+        // the chunks left of it are consecutive (hi and width are convex), those right of it
+        // too (lo is concave), so their ends are found by bisection
+        auto seek = [&](int c, int end, int step) {
+            while (c != end + step) {
+                const FanReach f = reach(c);
+                const bool l = left(f);
+                if (!l && !right(f)) return c;
+                auto out = [&](int x) { return l ? left(reach(x)) : right(reach(x)); };
+                int in = end;
+                if (out(in)) return end + step;
+                while (in - c != step) {
+                    const int mid = c + (in - c) / 2;
+                    (out(mid) ? c : in) = mid;
+                }
+                c = in;
             }
-        for (int c = nch - 1; c >= 0; --c)
-            if (const int f = chunk(c)) return f > 0;
-        return true;
+            return c;
+        };
+        auto fits = [](const FanReach& f) {
+            return f.width <= kFanTaps - 0.01 && f.hi - f.lo + std::ceil(f.width) + 4.5 <= (double)kFanCells;
+        };
+        const int c0 = seek(0, nch - 1, 1);
+        return c0 == nch || (fits(reach(c0)) && fits(reach(seek(nch - 1, 0, -1))));
     };
     for (int A = kProjWaves; A >= 1; A >>= 1) {
         bool fits = true;
