@@ -38,9 +38,9 @@ for dt, kernel in ((1.0, "fan_staged_kernel"), (4.0, "fan_project_kernel")):
     for i in range(3):
         g = fbp.Geometry(1441, int(1700 / dt), 1024, dt, np.arange(1441) * (2.0 * math.pi / 1441) + 0.001 * i, source_distance=2500.0)
         fake.fake_reset()
-        t = time.process_time()
+        t = time.thread_time()
         assert call("fbp_project", g, 1, A, C) == 0
-        times.append(time.process_time() - t)
+        times.append(time.thread_time() - t)
         assert launched()[-1][0] == kernel
     result.append(min(times))
 """)
