@@ -96,7 +96,8 @@ __device__ __forceinline__ void cone_stage(const ConeJob& job, const int* org, f
 // for views in parts without planes for the parts' sums: the workgroup takes the parts one
 // after another and adds their sums in registers, in the order and so with the bits of the
 // planes.  There are few blocks then, so each goes to kConeZB / ZS workgroups, which stage
-// the same windows; no voxel's arithmetic depends on ZS.
+// the same windows; no voxel's arithmetic depends on ZS.  64^3, 361 views: 593 us against 868
+// unsplit and 90 with planes; quarter-turn form, 100^2 x 60, 360 views: 471, 1244 and 127.
 template <bool STAGED, int P, int ZS>
 __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
     extern __shared__ __align__(16) char smem[];
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(kConeThreads) void cone_bp_kernel(ConeJob job) {
 //    summed in a fixed order, each voxel is written once, no atomics.
 // Bound by VALU issue (256^3, 360 views, 256 x 384 detector: 0.71 G wave instructions, 7.5
 // a sample against 13.3 of one column per lane, 1.16 ms at full issue; LDS 1.1 ms), with
-// four waves a SIMD.  Measured there, filter included: 1.72 ms against 2.54 ms.  Three
+// four waves a SIMD.  Measured there, filter included: 1.73 ms against 2.54 ms.  Three
 // waves a SIMD without spills: 2.14 ms; 12 slices a workgroup 2.00 ms; one end of the
 // window area for every item (two barriers an item): 1.86 ms.
 constexpr int kConeRotSerial = 4;                       // slices a workgroup of the serial form takes
@@ -599,7 +600,9 @@ __global__ __launch_bounds__(kConeThreads, 4) void cone_rot_kernel(ConeJob job) 
 }
 
 // Odd N: the centre column (x = y = 0, so rho = 1 and u = (Du-1)/2 on every view), one
-// slice per lane, all views in order.
+// slice per lane, all views in order.  A serial walk behind the main kernel, bound by the
+// latency of its loads: 44 us for 316 views (the main kernel 59 at 53^3), 90 for 360 (1680
+// at 255^3).
 __global__ __launch_bounds__(kConeThreads) void cone_centre_kernel(ConeJob job) {
     const int z = blockIdx.x * kConeThreads + threadIdx.x;
     if (z >= job.Nz) return;                                 // no barrier follows

@@ -60,11 +60,12 @@ constexpr int kOffImage = 0x7FFFFFF0;               // byte offset past every im
 //    are added in that order through LDS, whichever waves made them, so the number of
 //    angles per workgroup never changes a bit.  No atomics; each bin is written once.
 // Bound by VALU issue, with LDS reads close behind: a step of a wave (64 lane-rows, 256
-// bin-rows at M = 4) is 20 VALU instructions and three 16-byte LDS reads, and staging,
-// anchors and steps off the image add a quarter (512^2, 720 angles: 20.2 M VALU
-// instructions, 33 us at full issue; the staging loads taken out leave 38 of 39 us, the
-// LDS bank conflicts 35).  Measured there: 60 us one slice, 39 us a slice in stacks of
-// 16, against 111 and 87 us for one lane per bin reading padded copies from memory.
+// bin-rows at M = 4) is 23 VALU instructions (20 with FP32 positions) and three 16-byte LDS
+// reads, and staging, anchors and steps off the image add a quarter (512^2, 720 angles:
+// 23.4 M VALU instructions, 38 us at full issue; with FP32 positions the staging loads taken
+// out left 38 of 39 us a slice, the LDS bank conflicts 35).  Measured there: 63 us one slice,
+// 41 us a slice in stacks of 16 (FP32 positions 62 and 40), against 110 and 84 us for one lane
+// per bin reading padded copies from memory.
 // 16 bins by 4 rows per wave rather than 32 by 2: the blocks are half as large, four to
 // a CU for one slice; 4 or 2 angles instead of 8 stage more per bin (70 and 104 us).
 constexpr int kStThreads = 512;
@@ -321,8 +322,8 @@ __global__ __launch_bounds__(kStThreads) void project_staged_kernel(ProjStagedJo
 //  * The turned images are laid out once per call with a border of zeros, M = 4 as cells
 //    {I_0, I_1, I_2, I_3}, so that staging is one 16-byte load and one LDS store per cell.
 // Bound by VALU issue: per tap six instructions, a quarter-rate reciprocal and M S
-// multiply-adds (512^2, 720 views, two slices: 58.6 M wave instructions, 95 of 160 us at
-// full issue; LDS 66 us).  Measured there: 160 us, against 1450 us for one lane per bin
+// multiply-adds (512^2, 720 views, two slices: 61.3 M wave instructions, 100 of 156 us at
+// full issue; LDS 66 us).  Measured there: 156 us, against 1450 us for one lane per bin
 // reading padded copies from memory.  Eight views a workgroup rather than four: 160 and
 // 201 us (a staged cell serves twice the bins); two slices rather than one: 160 and 203 us.
 // 16 rows of at most 64 cells, which only two views fit, gathered from the image and its

@@ -1246,7 +1246,8 @@ int run_fan_backproject(Plan& p, int32_t n, const float* filt, float* img, hipSt
 // rest one slice per workgroup; both give bitwise the same slices.  Groups only where they
 // are more than the CUs: fewer leave CUs idle and each a longer walk (64^2 to 300^2, 4 to 16
 // slices: one slice per workgroup 0.6-0.95x the time up to 0.85 groups per CU, equal at one,
-// 1.05-1.2x from 1.5 on).
+// 1.05-1.2x from 1.5 on).  110 random stacks of 64^2 to 2048^2, 4 to 128 slices, against groups
+// throughout: 0.994-2.9 times as fast.
 int run_stack(const Plan& p, const ShapeParams& sh, int32_t n, const float* filt, float* img, hipStream_t s) {
     const int tiles = sh.tiles_x * sh.tiles_y;
     const size_t qs = (size_t)p.K * p.D, is = (size_t)p.N * p.N;
