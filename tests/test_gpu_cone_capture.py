@@ -15,7 +15,8 @@ from paper_2109_02174_amd import phantom as ph
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("K,N,Nz", [(40, 33, 20), (42, 33, 20), (64, 32, 33), (150, 17, 5), (4, 24, 20), (36, 200, 130)])
+@pytest.mark.parametrize("K,N,Nz", [(40, 33, 20), (42, 33, 20), (64, 32, 33), (150, 17, 5), (4, 24, 20), (36, 200, 130),
+                                    (36, 17, 300)])    # windows too large for LDS: direct reads
 def test_replays_equal_the_eager_volume(K, N, Nz):
     R = 1.9 * N
     g = fbp.ConeGeometry(K, int(1.6 * N), int(1.4 * Nz) + 3, N, Nz, R)
